@@ -91,7 +91,7 @@ enum {
     AUV_ALGO_AUTO = 0,   /* dense form when the expected disk population is at
                             least max_pts / 2 (and 1 <= max_pts <= 32): many
                             nodes would exceed the cap; else sparse */
-    AUV_ALGO_SPARSE = 1, /* node windows scattered from each sounding */
+    AUV_ALGO_SPARSE = 1, /* every sounding within reach applied to each node */
     AUV_ALGO_DENSE = 2,  /* per-node ring search with a register top-k list;
                             needs 1 <= max_pts <= 32 and AUV_P_FP32_REBASE */
     AUV_ALGO_SPAN = 3    /* sparse, span form: (sounding, node) pairs packed 64

@@ -228,6 +228,11 @@ struct WinGeom {
 bool window_geometry(const IdwArgs &a, WinGeom *g);
 auv_status launch_idw_window(const auv_bin_view &bins, const IdwArgs &a, const WinGeom &g,
                              int pmode, hipStream_t st);
+// Gather form: whether it covers a call, and its launch (g: the linear node
+// lattice, or null).
+bool gather_covers(const auv_bin_view &bv, const IdwArgs &a);
+auv_status launch_idw_gather(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g,
+                             hipStream_t st);
 auv_status launch_idw_dense(const auv_bin_view &bins, const IdwArgs &a, int pmode,
                             hipStream_t st);
 auv_status launch_idw_window_prec(const auv_bin_view &bins, const IdwArgs &a,

@@ -131,6 +131,83 @@ __device__ inline float wfast(float d2, int pmode, float power, float inv_r2)
     return __builtin_amdgcn_exp2f(-0.5f * power * __builtin_amdgcn_logf(d2 * inv_r2));
 }
 
+// Outputs of node (row an, column b) from its ascending list of nearest keys
+// (D^2 << kb | index, as FP64 entries; the finite ones are the members): the
+// first max_pts of them are the selected set, summed in key order.
+template <int kMode, int KMAX>
+__device__ __forceinline__ void dense_finish(const auv_bin_view &bv, const IdwArgs &a, int b, int an,
+                                             const double (&list)[KMAX], int kb, int pmode)
+{
+    constexpr bool kIdw = (kMode & 1) != 0;
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    const auto gR = gmem(reinterpret_cast<const v4i *>(bv.rec));
+    const NodeL nx_l = node_lat(b, a.dx), ny_l = node_lat(an, a.dy);
+    const int Xn = nx_l.X, Yn = ny_l.X;
+    const int kcap = a.max_pts;  // 1 <= kcap <= KMAX
+    int m = 0;  // members taken: min(found, kcap)
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j)
+        m += (j < kcap && list[j] < __builtin_huge_val()) ? 1 : 0;
+    unsigned long long keys[KMAX];
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j)
+        keys[j] = key_of(list[j]);
+    const int64_t o = (int64_t)an * a.nx + b;
+    const unsigned long long imask = (1ull << kb) - 1ull;
+    if (kMode & 2) {
+        const int bi = m > 0 ? (int)(keys[0] & imask) : -1;
+        if (a.nn_idx_out)
+            gmem(a.nn_idx_out)[o] = bi;
+        if (a.nn_z_out)
+            gmem(a.nn_z_out)[o] = m > 0 ? __int_as_float(gR[bi].w) : NAN;
+    }
+    if constexpr (kIdw) {
+        if (a.cnt_out)
+            gmem(a.cnt_out)[o] = m;
+        float v;
+        if (m == 0) {
+            v = NAN;
+        } else if ((keys[0] >> kb) == 0ull) {
+            // hits: the members with D^2 == 0, in ascending index
+            double hs = 0.0;
+            int nh = 0;
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) {
+                if (j < m && (keys[j] >> kb) == 0ull) {
+                    hs += (double)__int_as_float(gR[(int)(keys[j] & imask)].w);
+                    ++nh;
+                }
+            }
+            v = (float)(hs / (double)nh);
+        } else if (m < a.min_pts) {
+            v = NAN;
+        } else {
+            const float z0 = __int_as_float(gR[(int)(keys[0] & imask)].w);
+            float num = 0.0f, den = 0.0f, zmin = z0, zmax = z0;
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) {
+                if (j < m) {
+                    const v4i r = gR[(int)(keys[j] & imask)];
+                    const float z = __int_as_float(r.w);
+                    const int qx = (int)(int16_t)((uint32_t)r.z & 0xffffu);
+                    const int qy = (int)(int16_t)((uint32_t)r.z >> 16);
+                    const float fx = (float)(r.x - Xn) + (float)(qx - nx_l.q) * kResidualUnit;
+                    const float fy = (float)(r.y - Yn) + (float)(qy - ny_l.q) * kResidualUnit;
+                    const float w = wfast(fx * fx + fy * fy, pmode, a.power, a.inv_r2);
+                    num += w * (z - z0);
+                    den += w;
+                    zmin = fminf(zmin, z);
+                    zmax = fmaxf(zmax, z);
+                }
+            }
+            double r = (double)z0 + (double)num / (double)den;
+            r = fmin(fmax(r, (double)zmin), (double)zmax);
+            v = (float)r;
+        }
+        gmem(a.z_out)[o] = v;
+    }
+}
+
 // Exact value of node (row an, column b) by one lane (no wave-wide operations,
 // so any subset of lanes may call it): ring search for the max_pts nearest
 // keys (max_pts <= KMAX), then the weighted sum in key order.  Writes the
@@ -139,13 +216,10 @@ template <int kMode, int KMAX>
 __device__ __forceinline__ void dense_node(const auv_bin_view &bv, const IdwArgs &a, int b, int an,
                                            int pmode)
 {
-    constexpr bool kIdw = (kMode & 1) != 0;
     // explicitly global pointers (descriptors read from memory would
     // otherwise give flat loads)
     const gptr<const int32_t> gX = gmem(bv.X), gY = gmem(bv.Y), gI = gmem(bv.idx);
     const auto gC = gmem(bv.cell_start);
-    typedef int v4i __attribute__((ext_vector_type(4)));
-    const auto gR = gmem(reinterpret_cast<const v4i *>(bv.rec));
     const NodeL nx_l = node_lat(b, a.dx), ny_l = node_lat(an, a.dy);
     const int Xn = nx_l.X, Yn = ny_l.X;
     const int s = bv.bin_log2;
@@ -244,68 +318,7 @@ __device__ __forceinline__ void dense_node(const auv_bin_view &bv, const IdwArgs
         }
     }
 
-    int m = 0;  // members taken: min(found, kcap)
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j)
-        m += (j < kcap && list[j] < __builtin_huge_val()) ? 1 : 0;
-    unsigned long long keys[KMAX];
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j)
-        keys[j] = key_of(list[j]);
-    const int64_t o = (int64_t)an * a.nx + b;
-    const unsigned long long imask = (1ull << kb) - 1ull;
-    if (kMode & 2) {
-        const int bi = m > 0 ? (int)(keys[0] & imask) : -1;
-        if (a.nn_idx_out)
-            gmem(a.nn_idx_out)[o] = bi;
-        if (a.nn_z_out)
-            gmem(a.nn_z_out)[o] = m > 0 ? __int_as_float(gR[bi].w) : NAN;
-    }
-    if constexpr (kIdw) {
-        if (a.cnt_out)
-            gmem(a.cnt_out)[o] = m;
-        float v;
-        if (m == 0) {
-            v = NAN;
-        } else if ((keys[0] >> kb) == 0ull) {
-            // hits: the members with D^2 == 0, in ascending index
-            double hs = 0.0;
-            int nh = 0;
-#pragma unroll
-            for (int j = 0; j < KMAX; ++j) {
-                if (j < m && (keys[j] >> kb) == 0ull) {
-                    hs += (double)__int_as_float(gR[(int)(keys[j] & imask)].w);
-                    ++nh;
-                }
-            }
-            v = (float)(hs / (double)nh);
-        } else if (m < a.min_pts) {
-            v = NAN;
-        } else {
-            const float z0 = __int_as_float(gR[(int)(keys[0] & imask)].w);
-            float num = 0.0f, den = 0.0f, zmin = z0, zmax = z0;
-#pragma unroll
-            for (int j = 0; j < KMAX; ++j) {
-                if (j < m) {
-                    const v4i r = gR[(int)(keys[j] & imask)];
-                    const float z = __int_as_float(r.w);
-                    const int qx = (int)(int16_t)((uint32_t)r.z & 0xffffu);
-                    const int qy = (int)(int16_t)((uint32_t)r.z >> 16);
-                    const float fx = (float)(r.x - Xn) + (float)(qx - nx_l.q) * kResidualUnit;
-                    const float fy = (float)(r.y - Yn) + (float)(qy - ny_l.q) * kResidualUnit;
-                    const float w = wfast(fx * fx + fy * fy, pmode, a.power, a.inv_r2);
-                    num += w * (z - z0);
-                    den += w;
-                    zmin = fminf(zmin, z);
-                    zmax = fmaxf(zmax, z);
-                }
-            }
-            double r = (double)z0 + (double)num / (double)den;
-            r = fmin(fmax(r, (double)zmin), (double)zmax);
-            v = (float)r;
-        }
-        gmem(a.z_out)[o] = v;
-    }
+    dense_finish<kMode, KMAX>(bv, a, b, an, list, kb, pmode);
 }
 
 // Whether the dense form's keys fit: (R^2 << index bits) plus the largest

@@ -1,0 +1,53 @@
+// Gather IDW form: launcher.  The per-tile code is in idw_gather_impl.hpp.
+#include "idw_gather_impl.hpp"
+
+namespace auv {
+
+using namespace gather;
+
+namespace {
+
+template <int kMode, bool kGen>
+void launch_pmode(const auv_bin_view &bv, const IdwArgs &a, const WinGeom &g, hipStream_t st)
+{
+    const int ntx = (a.nx + 7) / 8, nt = ntx * ((a.ny + 7) / 8);
+    const dim3 grid((unsigned)nt), block(64);
+    if (kMode == 2 || a.pmode == 2)
+        k_idw_gather<kMode, 2, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
+    else if (a.pmode != 0)
+        k_idw_gather<kMode, -1, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
+    else
+        k_idw_gather<kMode, 0, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
+}
+
+template <int kMode>
+void launch_lattice(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g, hipStream_t st)
+{
+    if (g && gather_linear(*g, a.R))
+        launch_pmode<kMode, false>(bv, a, *g, st);
+    else
+        launch_pmode<kMode, true>(bv, a, WinGeom{}, st);
+}
+
+}  // namespace
+
+bool gather_covers(const auv_bin_view &bv, const IdwArgs &a)
+{
+    return a.precision == AUV_P_FP32_REBASE && a.mode >= 1 && a.mode <= 3 &&
+           gather_ok(a.R, bv.idx_bits, a.max_pts) &&
+           (int64_t)((a.nx + 7) / 8) * ((a.ny + 7) / 8) < (int64_t(1) << 31);
+}
+
+auv_status launch_idw_gather(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g,
+                             hipStream_t st)
+{
+    switch (a.mode) {
+    case 1: launch_lattice<1>(bv, a, g, st); break;
+    case 2: launch_lattice<2>(bv, a, g, st); break;
+    default: launch_lattice<3>(bv, a, g, st); break;
+    }
+    AUV_HIP(hipGetLastError());
+    return AUV_OK;
+}
+
+}  // namespace auv
