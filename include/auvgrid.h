@@ -349,7 +349,9 @@ auv_status auv_batch_autotune(const auv_batch_item *items, int32_t count, void *
                               size_t ws_bytes, auv_stream stream, const char *tune_path);
 
 /* Per-item plan actually used (for reports): bin_log2, kernel form and node
- * tile per wave (columns, rows).  Every pointer is nullable. */
+ * tile per wave (columns, rows).  Where no tuning table set the bin size, the
+ * dense form subdivides these bins when they hold many soundings.  Every
+ * pointer is nullable. */
 auv_status auv_batch_item_plan(const auv_batch *batch, int32_t item, int32_t *bin_log2,
                                int32_t *algo, int32_t *tile_w, int32_t *tile_h);
 

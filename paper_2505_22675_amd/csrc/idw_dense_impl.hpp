@@ -286,36 +286,43 @@ __device__ __forceinline__ void dense_node(const auv_bin_view &bv, const IdwArgs
         }
     };
 
-    {
-        for (int d = 0;; ++d) {
-            // ring d: its top and bottom rows, then the left and right bins of
-            // the rows between (one loop, so the candidate code is inlined once)
-            const int nseg = d == 0 ? 1 : 4 * d;
-            for (int sg = 0; sg < nseg; ++sg) {
-                int row, c0, c1;
-                if (sg < 2) {
-                    row = sg == 0 ? byn - d : byn + d;
-                    c0 = bxn - d;
-                    c1 = bxn + d;
-                } else {
-                    row = byn - d + 1 + ((sg - 2) >> 1);
-                    c0 = c1 = (sg & 1) ? bxn + d : bxn - d;
-                }
-                segment(row, c0, c1);
+    // annuli of bins around the node's bin: rings dp + 1 .. d at once, as their
+    // full rows (above and below) and the left and right parts of the rows
+    // between (one loop, so the candidate code is inlined once).  One ring at
+    // a time, but while no lane of the wave has found anything the annulus
+    // doubles: a wave far from any sounding reads 2 segments per bin row of
+    // its reach instead of 4 d per ring.
+    for (int dp = -1, d = 0;;) {
+        const int nfull = dp < 0 ? 1 : 2 * (d - dp);
+        const int nseg = dp < 0 ? 1 : nfull + 2 * (2 * dp + 1);
+        for (int sg = 0; sg < nseg; ++sg) {
+            int row, c0, c1;
+            if (sg < nfull) {
+                row = (sg & 1) ? byn + d - (sg >> 1) : byn - d + (sg >> 1);
+                c0 = bxn - d;
+                c1 = bxn + d;
+            } else {
+                const int j = sg - nfull;
+                row = byn - dp + (j >> 1);
+                c0 = (j & 1) ? bxn + dp + 1 : bxn - d;
+                c1 = (j & 1) ? bxn + d : bxn - dp - 1;
             }
-            // every unvisited sounding is at least lb away
-            const long long lb = (long long)d * B + m0;
-            if (lb * lb > R2)
-                break;
-            // the cap-th key (a select chain over the list: an indexed read
-            // would copy the list into consecutive registers every ring)
-            double kth = list[0];
-#pragma unroll
-            for (int j = 1; j < KMAX; ++j)
-                kth = j == kcap - 1 ? list[j] : kth;
-            if (kth < __builtin_huge_val() && (long long)(key_of(kth) >> kb) < lb * lb)
-                break;
+            segment(row, c0, c1);
         }
+        // every unvisited sounding is at least lb away
+        const long long lb = (long long)d * B + m0;
+        if (lb * lb > R2)
+            break;
+        // the cap-th key (a select chain over the list: an indexed read
+        // would copy the list into consecutive registers every ring)
+        double kth = list[0];
+#pragma unroll
+        for (int j = 1; j < KMAX; ++j)
+            kth = j == kcap - 1 ? list[j] : kth;
+        if (kth < __builtin_huge_val() && (long long)(key_of(kth) >> kb) < lb * lb)
+            break;
+        dp = d;
+        d = __any(list[0] < __builtin_huge_val()) ? d + 1 : min(2 * d + 1, max(d, R >> s) + 1);
     }
 
     dense_finish<kMode, KMAX>(bv, a, b, an, list, kb, pmode);
