@@ -3,26 +3,22 @@
 //   auv_batch_plan      host: validate items, pick bin size and kernel form per
 //                       item (autotune table or defaults), lay out a workspace
 //   auv_batch_launch    first call: upload item tables, capture
-//                         batched binning (5 launches for all items)
-//                         -> queue reset -> one persistent IDW launch per
-//                         kernel form (sparse window / dense top-k, on two
-//                         concurrent branches), + per-item launches for items
-//                         they do not cover
+//                         batched binning (4 launches for all items)
+//                         -> one IDW launch per kernel form over the units of
+//                         all its items (sparse gather / dense top-k, on two
+//                         concurrent branches; span), + per-item launches for
+//                         items they do not cover
 //                       into a HIP graph; later calls replay the graph
 //   auv_batch_launch_plain  the same items one after another, default sizes
 //   auv_batch_autotune  time (bin size, form) candidates per item class
 //
-// The persistent kernels: each 64-lane wave takes its home queue (one per XCD:
-// blocks are dealt round-robin to the 8 XCDs, so block b runs on XCD b % 8),
-// pulls (item, tile) work with one atomic per tile, and moves on to the other
-// queues when its own is drained.  Items are assigned to queues by longest
-// processing time first on an estimated cost, so each XCD's L2 mostly sees
-// the bins of a few items.
-#include "idw_dense_impl.hpp"
+// A unit is one (item, node tile); block b of a form's launch takes one unit
+// of the form's list (deal_unit), and the hardware's block scheduler balances
+// units of uneven cost.  Items with the costliest tiles come first.
+#include "idw_gather_impl.hpp"
 #include "idw_span_impl.hpp"
 
 #include <algorithm>
-#include <type_traits>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -38,194 +34,98 @@ namespace auv {
 
 namespace {
 
-constexpr int kQueues = 8;
-constexpr int kBatchDenseK = 16;  // largest max_pts the persistent dense path keeps
-constexpr size_t kOvfMax = size_t(1) << 21;  // over-cap list entries at most (32 MiB)
+constexpr int kXcds = 8;
+constexpr int kRun = 64;  // consecutive units of one XCD
+constexpr int kForms = 3; // sparse, dense, span
+constexpr int kBatchDenseK = 16;  // largest max_pts the batched dense kernel keeps
+
+enum { kSparse = 0, kDense = 1, kSpan = 2 };
 
 struct IdwItem {
     auv_bin_view bv;
     IdwArgs a;
     WinGeom g;
     int32_t ntx, ntiles;
-    int32_t dense, pmode;
-    int32_t span;  // sparse items: the span form covers it (else the window form)
-    // window items: nodes above the cap go to the over-cap list (cap <= 16,
-    // dense keys fit), finished by k_overcap_dense after the persistent kernels
-    int32_t cap_list;
+    int32_t form, pmode;  // form: kSparse, kDense or kSpan
 };
 
-// Queue heads of both forms, then the over-cap list's entry count.
-__global__ void k_reset_queues(int32_t *qhead)
+// The unit of block b out of n: blocks are dealt round-robin to the 8 XCDs,
+// so each XCD gets runs of kRun consecutive units (neighbouring tiles of an
+// item, whose halos overlap in its L2) and every XCD a share of every item.
+// (Queues with one head per XCD and guided grabs took longer: every grab is a
+// device atomic on one of eight addresses, and the loop around a tile made the
+// compiler keep its constants in scratch.)
+__device__ inline int deal_unit(int b, int n)
 {
-    if (threadIdx.x < 2 * kQueues + 1)
-        qhead[threadIdx.x] = 0;
+    const int g = b / (kXcds * kRun), l = b - g * (kXcds * kRun);
+    return (g + 1) * (kXcds * kRun) <= n ? g * (kXcds * kRun) + (l & (kXcds - 1)) * kRun + l / kXcds
+                                         : b;
 }
 
-template <int kPmode, int kChunks>
-__device__ inline void run_window(const IdwItem &it, int tile, const win::WinSmem &sm,
-                                  win::CapSink sink)
-{
-    if (!it.cap_list)
-        sink.count = nullptr;
-    win::window_tile<3, kPmode, true, kChunks, AUV_P_FP32_REBASE>(it.bv, it.a, it.g, tile,
-                                                                  it.ntx, sm, 0, 1, nullptr, sink);
-}
+// One launch per form (their register and LDS budgets differ).  The work entry
+// is wave-uniform: the item descriptor is read with scalar loads.
 
-// The window items' nodes above the cap, one lane per node: the dense form's
-// ring search for the cap nearest.  Every tile of a wave's window kernel
-// re-did such nodes one at a time, the whole wave per node; clustered
-// soundings put hundreds of them in one tile.
-__global__ __launch_bounds__(64) void k_overcap_dense(const IdwItem *__restrict__ items,
-                                                      const int4 *__restrict__ list,
-                                                      const int32_t *__restrict__ count, int cap)
+// Sparse: a unit is 16 nodes wide and 16 or 8 high, one 8 x 8-node gather tile
+// per wave.  Bound by vector instruction issue like the gather form itself.
+// Against the persistent window kernel it replaced (LDS accumulators, work from
+// queues): 32 tiles of 512^2 nodes with 0.25 / 2 / 8 soundings per disk, binning
+// included, 699 / 716 / 912 -> 136 / 185 / 572 us (cap 16), 877 -> 385 us
+// (8 per disk, no cap).
+template <bool kGeneral>
+__global__ __launch_bounds__(256, 8) void k_idw_batch_sparse(const IdwItem *__restrict__ items,
+                                                             const int2 *__restrict__ work, int n)
 {
-    const int n = min(*count, cap);
-    for (int e = blockIdx.x * 64 + (int)threadIdx.x; e < n; e += gridDim.x * 64) {
-        const int4 v = list[e];
-        const IdwItem &it = items[v.x];
-        dense::dense_node<3, kBatchDenseK>(it.bv, it.a, v.z, v.y, it.pmode);
-    }
-}
-
-// Grab the next `grab` work entries of queue q: returns the first (or -1 when
-// the queue is drained).  One atomic per grab, issued by lane 0 and broadcast
-// (wave-uniform).  Grabbing several tiles at once matters: every wave pulls
-// from a few shared counters, and same-address device atomics serialise.
-__device__ inline int pull(int32_t *qhead, int q, int len, int grab)
-{
-    int t = 0;
-    if (threadIdx.x == 0)
-        t = atomicAdd(&qhead[q], grab);
-    t = __builtin_amdgcn_readfirstlane(t);
-    return t < len ? t : -1;
-}
-
-// Guided grab size: half of the tiles still unclaimed as last seen by this
-// wave (`seen`, the queue head after its previous grab) spread over the
-// `waves` sharing the queue, at most gmax, at least one.  The grabs shrink
-// toward one tile as the queue drains, so no wave is left with a long run of
-// expensive tiles at the end while the others idle.
-__device__ inline int grab_size(int seen, int len, int gmax, int waves)
-{
-    return max(1, min(gmax, (len - seen) / (2 * waves)));
-}
-
-// Persistent kernels, one per kernel form (the forms' register budgets differ
-// by 2x, so sharing one kernel would halve the occupancy of the sparse form).
-// Each wave starts on the queue of its own XCD and then drains the others.
-// The window kernel is instantiated with the span form (its LDS is the union
-// of both forms' arrays) and with a general power (a second window variant
-// with running log-weight maxima) only when some item needs them: each costs
-// LDS or registers, hence occupancy.
-template <bool kSpan, bool kGeneral>
-__global__ __launch_bounds__(64) void k_idw_batch_window(const IdwItem *__restrict__ items,
-                                                         const int2 *__restrict__ work,
-                                                         const int32_t *__restrict__ qoff,
-                                                         const int32_t *__restrict__ qgrab,
-                                                         int32_t *__restrict__ qhead, int qwaves,
-                                                         int4 *__restrict__ ovf_list, int ovf_cap)
-{
-    struct WinLds {
-        float2 nd[win::kAcc];
-        int cnt[win::kAcc];
-        float lo[win::kAcc];
-        float hi[win::kAcc];
-        unsigned long long key[win::kAcc];
-        float emax[kGeneral ? win::kAcc : 1];
-        int beg[win::kMaxRows];
-        int off[win::kMaxRows + 1];
-        int4 rec[win::kRecSlots];
-    };
-    struct NoSpan {
-        char pad[16];
-    };
-    using SpanLds = typename std::conditional<kSpan, span::Smem<win::kTW, win::kTH>, NoSpan>::type;
-    // one tile at a time: the span form's LDS and the window form's share
-    // the same bytes
-    __shared__ union {
-        SpanLds sp;
-        WinLds w;
-    } lds;
-    const win::WinSmem sm{lds.w.nd, lds.w.cnt, lds.w.lo, lds.w.hi, lds.w.key, nullptr, nullptr, nullptr,
-                          lds.w.emax, lds.w.beg, lds.w.off, lds.w.rec, lds.w.rec + 1, nullptr};
-    const int home = blockIdx.x & (kQueues - 1);
-    for (int k = 0; k < kQueues; ++k) {
-        const int q = (home + k) & (kQueues - 1);
-        const int len = qoff[q + 1] - qoff[q], gmax = qgrab[q];
-        int seen = 0;
-        for (int g = grab_size(seen, len, gmax, qwaves), t0 = pull(qhead, q, len, g); t0 >= 0;
-             seen = t0 + g, g = grab_size(seen, len, gmax, qwaves), t0 = pull(qhead, q, len, g)) {
-            // the grab's work entries, one per lane, read at once
-            const int tn = min(t0 + g, len) - t0;
-            const int lane = threadIdx.x & 63;
-            int2 wl = make_int2(0, 0);
-            if (lane < tn)
-                wl = work[qoff[q] + t0 + lane];
-            for (int t = 0; t < tn; ++t) {
-                // wave-uniform work entry: the item descriptor is then read
-                // with scalar loads into SGPRs instead of vector registers
-                const int2 w = make_int2(__builtin_amdgcn_readlane(wl.x, t),
-                                         __builtin_amdgcn_readlane(wl.y, t));
-                const IdwItem &it = items[w.x];
-                // integer powers share one variant (the power is a runtime
-                // value there); a general power needs the window form's
-                // rescaling variant
-                if constexpr (kSpan) {
-                    if (it.span) {
-                        __syncthreads();  // the previous tile is finished with the LDS
-                        span::span_tile<3, -1, win::kTW, win::kTH>(it.bv, it.a, it.g, w.y,
-                                                                   it.ntx, lds.sp);
-                        continue;
-                    }
-                }
-                // nodes above the cap go to the over-cap list (when there is one)
-                win::CapSink sk;
-                if (ovf_list) {
-                    sk.count = qhead + 2 * kQueues;
-                    sk.list = ovf_list;
-                    sk.cap = ovf_cap;
-                    sk.item = w.x;
-                }
-                if constexpr (kGeneral) {
-                    if (it.pmode == 0) {
-                        run_window<0, 1>(it, w.y, sm, sk);
-                        continue;
-                    }
-                }
-                run_window<-1, 1>(it, w.y, sm, sk);
-            }
+    __shared__ gather::Smem sm[4];
+    const int2 w = work[deal_unit(blockIdx.x, n)];
+    const IdwItem &it = items[w.x];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int uy = w.y / it.ntx, ux = w.y - uy * it.ntx;
+    const int sub = win::tile_rows(it.a) / 8;  // gather tile rows of a unit
+    const int tx = 2 * ux + (wave & 1), ty = sub * uy + (wave >> 1);
+    if ((wave >> 1) >= sub || tx * 8 >= it.a.nx || ty * 8 >= it.a.ny)
+        return;
+    // integer powers share one variant (the power is a runtime value there);
+    // a general power needs the rescaling variant
+    if constexpr (kGeneral) {
+        if (it.pmode == 0) {
+            gather::gather_tile<3, 0, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
+            return;
         }
     }
+    gather::gather_tile<3, -1, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
 }
 
+// Dense: one node tile of 64 nodes per block.
 __global__ __launch_bounds__(64) void k_idw_batch_dense(const IdwItem *__restrict__ items,
-                                                        const int2 *__restrict__ work,
-                                                        const int32_t *__restrict__ qoff,
-                                                        const int32_t *__restrict__ qgrab,
-                                                        int32_t *__restrict__ qhead, int qwaves)
+                                                        const int2 *__restrict__ work, int n)
 {
-    const int home = blockIdx.x & (kQueues - 1);
-    for (int k = 0; k < kQueues; ++k) {
-        const int q = (home + k) & (kQueues - 1);
-        const int len = qoff[q + 1] - qoff[q], gmax = qgrab[q];
-        int seen = 0;
-        for (int g = grab_size(seen, len, gmax, qwaves), t0 = pull(qhead, q, len, g); t0 >= 0;
-             seen = t0 + g, g = grab_size(seen, len, gmax, qwaves), t0 = pull(qhead, q, len, g)) {
-            // the grab's work entries, one per lane, read at once
-            const int tn = min(t0 + g, len) - t0;
-            const int lane = threadIdx.x & 63;
-            int2 wl = make_int2(0, 0);
-            if (lane < tn)
-                wl = work[qoff[q] + t0 + lane];
-            for (int t = 0; t < tn; ++t) {
-                // wave-uniform work entry (scalar loads of the descriptor)
-                const int2 w = make_int2(__builtin_amdgcn_readlane(wl.x, t),
-                                         __builtin_amdgcn_readlane(wl.y, t));
-                const IdwItem &it = items[w.x];
-                dense::dense_tile<3, kBatchDenseK>(it.bv, it.a, w.y, it.ntx, it.pmode);
-            }
-        }
-    }
+    const int2 w = work[deal_unit(blockIdx.x, n)];
+    const IdwItem &it = items[w.x];
+    dense::dense_tile<3, kBatchDenseK>(it.bv, it.a, w.y, it.ntx, it.pmode);
+}
+
+// Span: one 16 x 16 node tile per block.
+__global__ __launch_bounds__(64) void k_idw_batch_span(const IdwItem *__restrict__ items,
+                                                       const int2 *__restrict__ work, int n)
+{
+    __shared__ span::Smem<win::kTW, win::kTH> sm;
+    const int2 w = work[deal_unit(blockIdx.x, n)];
+    const IdwItem &it = items[w.x];
+    span::span_tile<3, -1, win::kTW, win::kTH>(it.bv, it.a, it.g, w.y, it.ntx, sm);
+}
+
+void launch_form(int form, bool general, const IdwItem *items, const int2 *work, int n,
+                 hipStream_t st)
+{
+    const dim3 grid((unsigned)n);
+    if (form == kDense)
+        k_idw_batch_dense<<<grid, 64, 0, st>>>(items, work, n);
+    else if (form == kSpan)
+        k_idw_batch_span<<<grid, 64, 0, st>>>(items, work, n);
+    else if (general)
+        k_idw_batch_sparse<true><<<grid, 256, 0, st>>>(items, work, n);
+    else
+        k_idw_batch_sparse<false><<<grid, 256, 0, st>>>(items, work, n);
 }
 
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -364,18 +264,16 @@ struct auv_batch {
     std::vector<auv::Choice> tile;         // batched form: node tile per wave
     std::vector<size_t> slice_off;         // per-item workspace slice
     std::vector<size_t> slice_size;
-    std::vector<uint8_t> persistent;       // covered by the persistent kernel
+    std::vector<uint8_t> covered;          // by the forms' batched kernels
     size_t tables_bytes = 0, ws_bytes = 0;
     // host copies of the device tables (valid for `bound_ws`)
     std::vector<auv::RowItem> rows;
     std::vector<auv::IdwItem> idw;
-    std::vector<int32_t> offs;  // hist, scatter, sort offsets, then qoff
+    std::vector<int32_t> offs;  // hist, scatter, sort offsets
     std::vector<int2> work;
     int32_t hist_blocks = 0, scatter_blocks = 0, sort_blocks = 0, nrow_items = 0;
-    int32_t nwork_window = 0, nwork_dense = 0;
-    int32_t blocks_window = 0, blocks_dense = 0;  // persistent grid sizes
-    bool any_span = false, any_general = false;    // window items needing those variants
-    int32_t ovf_cap = 0;                           // entries of the over-cap list
+    int32_t work_off[auv::kForms + 1] = {0, 0, 0, 0};  // each form's units in `work`
+    bool any_general = false;  // a sparse item with a general power
     int32_t max_nbx = 0, max_nby = 0;  // largest bin domain of the row-binned items
     double keys_per_row = 0.0;          // largest mean of soundings per bin row
     hipStream_t cap_stream2 = nullptr;
@@ -499,8 +397,8 @@ std::map<ClassKey, Choice> read_tune(const char *path)
     return t;
 }
 
-// The persistent kernels' descriptor of one item; false when they do not
-// cover it (window over 64 cells, key over 64 bits, cap above the dense limit).
+// The batched kernels' descriptor of one item; false when they do not cover it
+// (a node lattice that is not linear, a cap above the forms' limits).
 bool make_idw_item(const auv_batch_item &it, const auv_bin_view &bv, const IdwArgs &a,
                    int32_t algo, IdwItem *out)
 {
@@ -508,27 +406,20 @@ bool make_idw_item(const auv_batch_item &it, const auv_bin_view &bv, const IdwAr
     d.bv = bv;
     d.a = a;
     d.pmode = pmode_of(it.params.power);
-    d.dense = algo == AUV_ALGO_DENSE;
-    d.span = 0;
     bool ok = true;
-    if (d.dense) {
+    if (algo == AUV_ALGO_DENSE) {
+        d.form = kDense;
         ok = it.params.max_pts >= 1 && it.params.max_pts <= kBatchDenseK &&
              dense::dense_key_ok(a.R, bv.idx_bits);
         const int tw = dense::dense_tile_w(a), th = 64 / tw;
         d.ntx = (it.grid.nx + tw - 1) / tw;
         d.ntiles = d.ntx * ((it.grid.ny + th - 1) / th);
     } else {
-        ok = window_geometry(a, &d.g) && d.g.nchunks == 1;
-        const unsigned __int128 top = (unsigned __int128)((unsigned long long)a.R * a.R)
-                                      << bv.idx_bits;
-        ok = ok && top < ((unsigned __int128)1 << 64);
-        d.span = ok && a.span && span::span_ok(bv, a, d.g, d.pmode) ? 1 : 0;
-        d.cap_list = ok && !d.span && it.params.max_pts >= 1 &&
-                             it.params.max_pts <= kBatchDenseK &&
-                             dense::dense_key_ok(a.R, bv.idx_bits)
-                         ? 1
-                         : 0;
-        const int th = win::tile_rows(a);
+        ok = window_geometry(a, &d.g);
+        d.form = ok && a.span && span::span_ok(bv, a, d.g, d.pmode) ? kSpan : kSparse;
+        ok = ok && (d.form == kSpan || (gather::gather_linear(d.g, a.R) &&
+                                        gather::gather_ok(a.R, bv.idx_bits, it.params.max_pts)));
+        const int th = d.form == kSpan ? win::kTH : win::tile_rows(a);
         d.ntx = (it.grid.nx + win::kTW - 1) / win::kTW;
         d.ntiles = d.ntx * ((it.grid.ny + th - 1) / th);
     }
@@ -546,7 +437,7 @@ auv_status build_tables(auv_batch *b, char *ws)
     b->idw.assign(count, IdwItem{});
     b->row_items.clear();
     std::vector<int32_t> hist(1, 0), scat(1, 0), sort(1, 0);
-    std::vector<double> cost(count, 0.0), tile_cost(count, 0.0);
+    std::vector<double> tile_cost(count, 0.0);
     for (int i = 0; i < count; ++i) {
         const auv_batch_item &it = b->items[i];
         BinWorkspace w;
@@ -567,12 +458,12 @@ auv_status build_tables(auv_batch *b, char *ws)
         }
         IdwItem &d = b->idw[i];
         const bool ok = make_idw_item(it, bv, a, b->algo[i], &d) && row_path_ok(b->geom[i]);
-        b->persistent[i] = ok ? 1 : 0;
-        if (d.dense) {
-            cost[i] = (double)it.n + (double)it.grid.nx * it.grid.ny * 4.0;
-            tile_cost[i] = cost[i] / std::max(1, d.ntiles);
+        b->covered[i] = ok ? 1 : 0;
+        if (d.form == kDense) {
+            tile_cost[i] = ((double)it.n + (double)it.grid.nx * it.grid.ny * 4.0) /
+                           std::max(1, d.ntiles);
         } else {
-            // a window tile costs a fixed part plus one visit per sounding
+            // a tile costs a fixed part plus one visit per sounding
             // within reach of its box (uniform density over the grid grown
             // by the radius)
             const double r = it.params.radius;
@@ -581,78 +472,35 @@ auv_status build_tables(auv_batch *b, char *ws)
             const double bw = win::kTW * it.grid.dx + 2.0 * r;
             const double bh = win::tile_rows(a) * it.grid.dy + 2.0 * r;
             tile_cost[i] = 20.0 + rho * bw * bh;
-            cost[i] = tile_cost[i] * std::max(1, d.ntiles);
         }
     }
     b->nrow_items = (int32_t)b->row_items.size();
     b->hist_blocks = hist.back();
     b->scatter_blocks = scat.back();
     b->sort_blocks = sort.back();
-    // longest processing time first: items to the least loaded queue, one
-    // queue set per kernel form
+    // units by form, items with the costliest tiles first (a wave takes a tile
+    // alone, so a long tile late in the launch would end it late)
     std::vector<int> order(count);
     for (int i = 0; i < count; ++i)
         order[i] = i;
-    // items with the longest tiles first (a wave takes a tile alone, so a
-    // long tile late in a queue would end the kernel late); to the least
-    // loaded queue by total cost
-    std::sort(order.begin(), order.end(), [&](int x, int y) {
-        return tile_cost[x] != tile_cost[y] ? tile_cost[x] > tile_cost[y] : cost[x] > cost[y];
-    });
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int x, int y) { return tile_cost[x] > tile_cost[y]; });
     b->work.clear();
-    std::vector<int32_t> qoff(2 * kQueues + 1, 0);
-    for (int form = 0; form < 2; ++form) {
-        std::vector<std::vector<int>> q(kQueues);
-        std::vector<double> load(kQueues, 0.0);
+    b->any_general = false;
+    for (int form = 0; form < kForms; ++form) {
         for (int i : order) {
-            if (!b->persistent[i] || b->idw[i].dense != form)
+            if (!b->covered[i] || b->idw[i].form != form)
                 continue;
-            const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-            q[k].push_back(i);
-            load[k] += cost[i];
+            for (int t = 0; t < b->idw[i].ntiles; ++t)
+                b->work.push_back(make_int2(i, t));
+            b->any_general = b->any_general || (form == kSparse && b->idw[i].pmode == 0);
         }
-        for (int k = 0; k < kQueues; ++k) {
-            for (int i : q[k])
-                for (int t = 0; t < b->idw[i].ntiles; ++t)
-                    b->work.push_back(make_int2(i, t));
-            qoff[form * kQueues + k + 1] = (int32_t)b->work.size();
-        }
-    }
-    b->nwork_window = qoff[kQueues];
-    b->nwork_dense = qoff[2 * kQueues] - qoff[kQueues];
-    // tiles per grab: about 8 grabs per wave from its home queue
-    int dev = 0, cus = 256;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    // waves per CU of the two concurrent persistent kernels: the window
-    // kernel could hold 15 (its LDS, about 10.6 KB per wave) and the dense
-    // kernel 24 (80 registers), but they share the CUs.  Measured on the
-    // 256-tile batch: window 12 + dense 8 per CU 2.15 ms; window 16 + dense
-    // 8 2.33 ms, 10 + 8 2.16 ms, 8 + 8 2.27 ms; 16 + 12 2.43 ms, 16 + 6
-    // 2.33 ms, 16 + 4 2.67 ms.
-    b->blocks_window = std::max(1, std::min(b->nwork_window, cus * 12));
-    b->blocks_dense = std::max(1, std::min(b->nwork_dense, cus * 8));
-    b->any_span = b->any_general = false;
-    for (int i = 0; i < count; ++i) {
-        if (!b->persistent[i] || b->idw[i].dense)
-            continue;
-        b->any_span = b->any_span || b->idw[i].span;
-        b->any_general = b->any_general || b->idw[i].pmode == 0;
-    }
-    std::vector<int32_t> grab(2 * kQueues, 1);
-    for (int form = 0; form < 2; ++form) {
-        const int per_queue = std::max(1, (form ? b->blocks_dense : b->blocks_window) / kQueues);
-        for (int k = 0; k < kQueues; ++k) {
-            const int len = qoff[form * kQueues + k + 1] - qoff[form * kQueues + k];
-            grab[form * kQueues + k] = std::max(1, std::min(16, len / (8 * per_queue)));
-        }
+        b->work_off[form + 1] = (int32_t)b->work.size();
     }
     b->offs.clear();
     b->offs.insert(b->offs.end(), hist.begin(), hist.end());
     b->offs.insert(b->offs.end(), scat.begin(), scat.end());
     b->offs.insert(b->offs.end(), sort.begin(), sort.end());
-    b->offs.insert(b->offs.end(), qoff.begin(), qoff.end());
-    b->offs.insert(b->offs.end(), grab.begin(), grab.end());
     return AUV_OK;
 }
 
@@ -661,8 +509,6 @@ struct Tables {
     RowItem *rows;
     IdwItem *idw;
     int32_t *offs;
-    int32_t *qhead;
-    int4 *ovf;  // over-cap list
     int2 *work;
 };
 
@@ -676,41 +522,16 @@ Tables table_ptrs(const auv_batch *b, char *ws)
     t.idw = reinterpret_cast<IdwItem *>(ws + off);
     off += align256(sizeof(IdwItem) * count);
     t.offs = reinterpret_cast<int32_t *>(ws + off);
-    off += align256(sizeof(int32_t) * (3 * (count + 1) + 4 * kQueues + 1));
-    t.qhead = reinterpret_cast<int32_t *>(ws + off);
-    off += align256(sizeof(int32_t) * (2 * kQueues + 1));
-    t.ovf = reinterpret_cast<int4 *>(ws + off);
-    off += align256(sizeof(int4) * (size_t)b->ovf_cap);
+    off += align256(sizeof(int32_t) * 3 * (count + 1));
     t.work = reinterpret_cast<int2 *>(ws + off);
     return t;
 }
 
-size_t tables_size(size_t count, size_t max_tiles, size_t ovf_cap)
+size_t tables_size(size_t count, size_t max_tiles)
 {
     return align256(sizeof(RowItem) * count) + align256(sizeof(IdwItem) * count) +
-           align256(sizeof(int32_t) * (3 * (count + 1) + 4 * kQueues + 1)) +
-           align256(sizeof(int32_t) * (2 * kQueues + 1)) + align256(sizeof(int4) * ovf_cap) +
+           align256(sizeof(int32_t) * 3 * (count + 1)) +
            align256(sizeof(int2) * std::max<size_t>(max_tiles, 1));
-}
-
-void launch_batch_window(int blocks, bool any_span, bool any_general, const IdwItem *idw,
-                         const int2 *work, const int32_t *qoff, const int32_t *qgrab,
-                         int32_t *qhead, int4 *ovf_list, int ovf_cap, hipStream_t st)
-{
-    const int qw = std::max(1, blocks / kQueues);
-    const unsigned nb = (unsigned)blocks;
-    if (any_span && any_general)
-        k_idw_batch_window<true, true><<<nb, 64, 0, st>>>(idw, work, qoff, qgrab, qhead, qw,
-                                                           ovf_list, ovf_cap);
-    else if (any_span)
-        k_idw_batch_window<true, false><<<nb, 64, 0, st>>>(idw, work, qoff, qgrab, qhead, qw,
-                                                            ovf_list, ovf_cap);
-    else if (any_general)
-        k_idw_batch_window<false, true><<<nb, 64, 0, st>>>(idw, work, qoff, qgrab, qhead, qw,
-                                                            ovf_list, ovf_cap);
-    else
-        k_idw_batch_window<false, false><<<nb, 64, 0, st>>>(idw, work, qoff, qgrab, qhead, qw,
-                                                             ovf_list, ovf_cap);
 }
 
 // Enqueue the whole batched form on `st` (captured by the caller).
@@ -732,38 +553,27 @@ auv_status enqueue_batched(auv_batch *b, char *ws, hipStream_t st)
         const auv_batch_item &it = b->items[i];
         AUV_TRY_S(launch_binning(&b->grids[i], b->geom[i], it.x, it.y, it.z, it.n, w, st));
     }
-    if (!b->work.empty()) {
-        k_reset_queues<<<1, 64, 0, st>>>(t.qhead);
-        const int32_t *qoff = t.offs + 3 * (nr + 1);
-        const int32_t *qgrab = qoff + 2 * kQueues + 1;
-        // the dense form runs on a forked branch of the graph, concurrently
-        if (b->nwork_dense > 0) {
-            AUV_HIP(hipEventRecord(b->ev_fork, st));
-            AUV_HIP(hipStreamWaitEvent(b->cap_stream2, b->ev_fork, 0));
-            k_idw_batch_dense<<<b->blocks_dense, 64, 0, b->cap_stream2>>>(
-                t.idw, t.work, qoff + kQueues, qgrab + kQueues, t.qhead + kQueues,
-                std::max(1, b->blocks_dense / kQueues));
-            AUV_HIP(hipGetLastError());
-            AUV_HIP(hipEventRecord(b->ev_join, b->cap_stream2));
-        }
-        if (b->nwork_window > 0)
-            launch_batch_window(b->blocks_window, b->any_span, b->any_general, t.idw, t.work,
-                                qoff, qgrab, t.qhead, b->ovf_cap > 0 ? t.ovf : nullptr,
-                                b->ovf_cap, st);
-        AUV_HIP(hipGetLastError());
-        if (b->nwork_dense > 0)
-            AUV_HIP(hipStreamWaitEvent(st, b->ev_join, 0));
-        if (b->nwork_window > 0 && b->ovf_cap > 0) {
-            int dev = 0, cus = 256;
-            (void)hipGetDevice(&dev);
-            (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-            k_overcap_dense<<<cus * 4, 64, 0, st>>>(t.idw, t.ovf, t.qhead + 2 * kQueues,
-                                                    b->ovf_cap);
+    auto units = [&](int form) { return b->work_off[form + 1] - b->work_off[form]; };
+    auto launch = [&](int form, hipStream_t s) -> auv_status {
+        if (units(form) > 0) {
+            launch_form(form, b->any_general, t.idw, t.work + b->work_off[form], units(form), s);
             AUV_HIP(hipGetLastError());
         }
+        return AUV_OK;
+    };
+    // the dense form runs on a forked branch of the graph, concurrently
+    if (units(kDense) > 0) {
+        AUV_HIP(hipEventRecord(b->ev_fork, st));
+        AUV_HIP(hipStreamWaitEvent(b->cap_stream2, b->ev_fork, 0));
+        AUV_TRY_S(launch(kDense, b->cap_stream2));
+        AUV_HIP(hipEventRecord(b->ev_join, b->cap_stream2));
     }
+    AUV_TRY_S(launch(kSparse, st));
+    AUV_TRY_S(launch(kSpan, st));
+    if (units(kDense) > 0)
+        AUV_HIP(hipStreamWaitEvent(st, b->ev_join, 0));
     for (int i = 0; i < count; ++i) {
-        if (b->persistent[i])
+        if (b->covered[i])
             continue;
         AUV_TRY_S(launch_idw(b->idw[i].bv, b->idw[i].a, st));
     }
@@ -797,9 +607,9 @@ auv_status auv_batch_plan(const auv_batch_item *items, int32_t count, const char
     b->tile.resize(count);
     b->slice_off.resize(count);
     b->slice_size.resize(count);
-    b->persistent.assign(count, 0);
+    b->covered.assign(count, 0);
     const std::map<ClassKey, Choice> tune = read_tune(tune_path);
-    size_t off = 0, max_tiles = 0, ovf_nodes = 0;
+    size_t off = 0, max_tiles = 0;
     for (int i = 0; i < count; ++i) {
         const auv_batch_item &it = b->items[i];
         auv_status st = validate_item(it, i);
@@ -853,14 +663,8 @@ auv_status auv_batch_plan(const auv_batch_item *items, int32_t count, const char
         b->slice_size[i] = align256(need);
         const size_t tiles8 = (size_t)((it.grid.nx + 7) / 8) * ((it.grid.ny + 7) / 8);
         max_tiles += tiles8;
-        // over-cap list: room for every node of the capped window items, up
-        // to a bound (nodes beyond it are re-done inside their tiles)
-        if (b->algo[i] != AUV_ALGO_DENSE && it.params.max_pts >= 1 &&
-            it.params.max_pts <= kBatchDenseK)
-            ovf_nodes += (size_t)it.grid.nx * (size_t)it.grid.ny;
     }
-    b->ovf_cap = (int32_t)std::min<size_t>(ovf_nodes, kOvfMax);
-    b->tables_bytes = align256(tables_size(count, max_tiles, (size_t)b->ovf_cap));
+    b->tables_bytes = align256(tables_size(count, max_tiles));
     off = b->tables_bytes;
     for (int i = 0; i < count; ++i) {
         b->slice_off[i] = off;
@@ -1022,10 +826,10 @@ auv_status auv_batch_autotune(const auv_batch_item *items, int32_t count, void *
         float best_ms = 1e30f;
         // min of three timed runs (after one untimed) of binning + IDW
         // Time of a candidate in the setting it will run in: binning the item
-        // (min of three runs after one untimed), plus the persistent kernel of
+        // (min of three runs after one untimed), plus the batched kernel of
         // its form over enough repetitions of the item's tiles to fill the
         // chip (all reading the same bins), per repetition; items the
-        // persistent kernels do not cover get their own IDW launch instead.
+        // batched kernels do not cover get their own IDW launch instead.
         auto time_choice = [&](const Choice &c, float *out_ms) -> auv_status {
             *out_ms = 1e30f;
             BinGeom gg;
@@ -1069,31 +873,13 @@ auv_status auv_batch_autotune(const auv_batch_item *items, int32_t count, void *
             std::vector<int2> work(nwork);
             for (int t = 0; t < nwork; ++t)
                 work[t] = make_int2(0, t % d.ntiles);
-            const int blocks = std::max(1, std::min(nwork, cus * (d.dense ? 8 : 16)));
-            const int per_queue = std::max(1, blocks / kQueues);
-            std::vector<int32_t> offs(2 * kQueues + 1);
-            for (int k = 0; k <= kQueues; ++k)
-                offs[k] = (int32_t)((int64_t)nwork * k / kQueues);
-            for (int k = 0; k < kQueues; ++k)
-                offs[kQueues + 1 + k] =
-                    std::max(1, std::min(16, (offs[k + 1] - offs[k]) / (8 * per_queue)));
             const Tables t = table_ptrs(b, base);
             AUV_HIP(hipMemcpyAsync(t.idw, &d, sizeof(d), hipMemcpyHostToDevice, st));
             AUV_HIP(hipMemcpyAsync(t.work, work.data(), sizeof(int2) * nwork,
                                    hipMemcpyHostToDevice, st));
-            AUV_HIP(hipMemcpyAsync(t.offs, offs.data(), sizeof(int32_t) * offs.size(),
-                                   hipMemcpyHostToDevice, st));
             AUV_TRY_S(min_of_runs(
                 [&]() -> auv_status {
-                    k_reset_queues<<<1, 64, 0, st>>>(t.qhead);
-                    if (d.dense)
-                        k_idw_batch_dense<<<blocks, 64, 0, st>>>(t.idw, t.work, t.offs,
-                                                                 t.offs + kQueues + 1, t.qhead,
-                                                                 per_queue);
-                    else
-                        launch_batch_window(blocks, d.span != 0, d.pmode == 0, t.idw, t.work,
-                                            t.offs, t.offs + kQueues + 1, t.qhead, nullptr, 0,
-                                            st);
+                    launch_form(d.form, d.pmode == 0, t.idw, t.work, nwork, st);
                     AUV_HIP(hipGetLastError());
                     return AUV_OK;
                 },
