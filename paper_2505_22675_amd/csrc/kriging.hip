@@ -67,6 +67,127 @@ __device__ inline int window_start(double u, int n)
     return min(max(c - 2, 0), n - 5);
 }
 
+// 1 - exp(-t) from t = h / range (kSeries: Taylor series to t^7, t <= 1/4) or
+// from t log2(e).
+template <bool kSeries>
+__device__ __forceinline__ float one_minus_exp(float t)
+{
+    if constexpr (kSeries) {
+        // t (1 - t/2 (1 - t/3 (... (1 - t/7))))
+        float g = fmaf(-t, 1.0f / 7.0f, 1.0f);
+        g = fmaf(-t * (1.0f / 6.0f), g, 1.0f);
+        g = fmaf(-t * (1.0f / 5.0f), g, 1.0f);
+        g = fmaf(-t * (1.0f / 4.0f), g, 1.0f);
+        g = fmaf(-t * (1.0f / 3.0f), g, 1.0f);
+        g = fmaf(-t * 0.5f, g, 1.0f);
+        return t * g;
+    } else {
+        return 1.0f - __builtin_amdgcn_exp2f(-t);
+    }
+}
+
+// Mirror transform of a window per row (x), then per column (y); component
+// order per axis: sums 0+4, 1+3, 2 | differences 0-4, 1-3.
+__device__ __forceinline__ void mirror(float (&d)[25])
+{
+    float t[25];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        t[k * 5 + 0] = d[k * 5 + 0] + d[k * 5 + 4];
+        t[k * 5 + 1] = d[k * 5 + 1] + d[k * 5 + 3];
+        t[k * 5 + 2] = d[k * 5 + 2];
+        t[k * 5 + 3] = d[k * 5 + 0] - d[k * 5 + 4];
+        t[k * 5 + 4] = d[k * 5 + 1] - d[k * 5 + 3];
+    }
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        d[0 * 5 + i] = t[0 * 5 + i] + t[4 * 5 + i];
+        d[1 * 5 + i] = t[1 * 5 + i] + t[3 * 5 + i];
+        d[2 * 5 + i] = t[2 * 5 + i];
+        d[3 * 5 + i] = t[0 * 5 + i] - t[4 * 5 + i];
+        d[4 * 5 + i] = t[1 * 5 + i] - t[3 * 5 + i];
+    }
+}
+
+// Back to nodes: transpose of the mirror transform, y then x.
+__device__ __forceinline__ void mirror_back(const float (&u)[25], float (&w)[25])
+{
+    float t[25];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        t[0 * 5 + i] = u[0 * 5 + i] + u[3 * 5 + i];
+        t[4 * 5 + i] = u[0 * 5 + i] - u[3 * 5 + i];
+        t[1 * 5 + i] = u[1 * 5 + i] + u[4 * 5 + i];
+        t[3 * 5 + i] = u[1 * 5 + i] - u[4 * 5 + i];
+        t[2 * 5 + i] = u[2 * 5 + i];
+    }
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        w[k * 5 + 0] = t[k * 5 + 0] + t[k * 5 + 3];
+        w[k * 5 + 4] = t[k * 5 + 0] - t[k * 5 + 3];
+        w[k * 5 + 1] = t[k * 5 + 1] + t[k * 5 + 4];
+        w[k * 5 + 3] = t[k * 5 + 1] - t[k * 5 + 4];
+        w[k * 5 + 2] = t[k * 5 + 2];
+    }
+}
+
+// K^-1 (v, unbias) in the mirror basis, in place, for an unbiasedness entry of
+// 1 or 0; `last` gets the product's unbiasedness entry (without the part that
+// the entry 1 itself would add).  The blocks are read from the argument segment
+// through scalar loads: an opaque pointer keeps the 178 values from being held
+// in registers across the caller's loop.
+__device__ __forceinline__ void inverse_blocks(float (&v)[25], bool unbias, float &last)
+{
+    cfloat *mb = (cfloat *)((const __attribute__((address_space(4))) char *)
+                                __builtin_amdgcn_kernarg_segment_ptr() +
+                            offsetof(KrigArgs, mb));
+    asm volatile("" : "+s"(mb));
+    float u[25];
+    // even-even: y components 0..2, x components 0..2, then the unbiasedness
+    // row (the inverse is symmetric: that row is its column too)
+#pragma unroll
+    for (int r = 0; r < 10; ++r) {
+        float acc = unbias && r < 9 ? mb[90 - 9 + r] : 0.0f;
+#pragma unroll
+        for (int c = 0; c < 9; ++c)
+            acc = fmaf(mb[r * 9 + c], v[(c / 3) * 5 + c % 3], acc);
+        if (r < 9)
+            u[(r / 3) * 5 + r % 3] = acc;
+        else
+            last = acc;
+    }
+    // even-odd: y 0..2, x 3..4
+#pragma unroll
+    for (int r = 0; r < 6; ++r) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 6; ++c)
+            acc = fmaf(mb[90 + r * 6 + c], v[(c / 2) * 5 + 3 + c % 2], acc);
+        u[(r / 2) * 5 + 3 + r % 2] = acc;
+    }
+    // odd-even: y 3..4, x 0..2
+#pragma unroll
+    for (int r = 0; r < 6; ++r) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 6; ++c)
+            acc = fmaf(mb[126 + r * 6 + c], v[(3 + c / 3) * 5 + c % 3], acc);
+        u[(3 + r / 3) * 5 + r % 3] = acc;
+    }
+    // odd-odd: y 3..4, x 3..4
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            acc = fmaf(mb[162 + r * 4 + c], v[(3 + c / 2) * 5 + 3 + c % 2], acc);
+        u[(3 + r / 2) * 5 + 3 + r % 2] = acc;
+    }
+#pragma unroll
+    for (int q = 0; q < 25; ++q)
+        v[q] = u[q];
+}
+
 // The inverse of the kriging matrix K = [G 1; 1' 0] splits as [A b; b' c]
 // with 1'A = 0 and 1'b = 1 (the weights A g + b sum to one for any g).  For
 // w = K^-1 (z - z_c, 0), sum_q w_q = 0, so with g_q = 1 - e_q,
@@ -163,22 +284,14 @@ __global__ __launch_bounds__(kKrigCols) void k_kriging(const KrigArgs p)
     #pragma unroll
                 for (int i = 0; i < 5; ++i) {
                     const float t = __builtin_amdgcn_sqrtf(ex2[i] + ey2);
-                    if constexpr (kSeries) {
-                        // 1 - exp(-t) = t (1 - t/2 (1 - t/3 (... (1 - t/7))))
-                        float g = fmaf(-t, 1.0f / 7.0f, 1.0f);
-                        g = fmaf(-t * (1.0f / 6.0f), g, 1.0f);
-                        g = fmaf(-t * (1.0f / 5.0f), g, 1.0f);
-                        g = fmaf(-t * (1.0f / 4.0f), g, 1.0f);
-                        g = fmaf(-t * (1.0f / 3.0f), g, 1.0f);
-                        g = fmaf(-t * 0.5f, g, 1.0f);
-                        e[k * 5 + i] = t * g;
-                    } else {
+                    if constexpr (kSeries)
+                        e[k * 5 + i] = one_minus_exp<true>(t);
+                    else
                         e[k * 5 + i] = __builtin_amdgcn_exp2f(-t);
-                    }
                 }
             }
         };
-        float w[26];
+        float w[25], w25 = 0.0f;
         auto dot = [&](const float (&e)[25]) {
             float acc = 0.0f;
     #pragma unroll
@@ -201,95 +314,9 @@ __global__ __launch_bounds__(kKrigCols) void k_kriging(const KrigArgs p)
                     bad |= !isfinite(z);
                     dz[q] = z - zc;
                 }
-                // mirror transform per row (x), then per column (y):
-                // component order per axis: sums 0+4, 1+3, 2 | differences 0-4, 1-3
-                float t[25];
-    #pragma unroll
-                for (int k = 0; k < 5; ++k) {
-                    const float *d = &dz[k * 5];
-                    t[k * 5 + 0] = d[0] + d[4];
-                    t[k * 5 + 1] = d[1] + d[3];
-                    t[k * 5 + 2] = d[2];
-                    t[k * 5 + 3] = d[0] - d[4];
-                    t[k * 5 + 4] = d[1] - d[3];
-                }
-                float sv[25];
-    #pragma unroll
-                for (int i = 0; i < 5; ++i) {
-                    sv[0 * 5 + i] = t[0 * 5 + i] + t[4 * 5 + i];
-                    sv[1 * 5 + i] = t[1 * 5 + i] + t[3 * 5 + i];
-                    sv[2 * 5 + i] = t[2 * 5 + i];
-                    sv[3 * 5 + i] = t[0 * 5 + i] - t[4 * 5 + i];
-                    sv[4 * 5 + i] = t[1 * 5 + i] - t[3 * 5 + i];
-                }
-                // the blocks are read from the argument segment through scalar
-                // loads here, once per window: an opaque pointer keeps the 178
-                // values from being held in registers across the row loop
-                cfloat *mb = (cfloat *)((const __attribute__((address_space(4))) char *)
-                                            __builtin_amdgcn_kernarg_segment_ptr() +
-                                        offsetof(KrigArgs, mb));
-                asm volatile("" : "+s"(mb));
-                float uv[25];
-                float u25;
-                // even-even: y components 0..2, x components 0..2, then the
-                // unbiasedness row
-    #pragma unroll
-                for (int r = 0; r < 10; ++r) {
-                    float acc = 0.0f;
-    #pragma unroll
-                    for (int c = 0; c < 9; ++c)
-                        acc = fmaf(mb[r * 9 + c], sv[(c / 3) * 5 + c % 3], acc);
-                    if (r < 9)
-                        uv[(r / 3) * 5 + r % 3] = acc;
-                    else
-                        u25 = acc;
-                }
-                // even-odd: y 0..2, x 3..4
-    #pragma unroll
-                for (int r = 0; r < 6; ++r) {
-                    float acc = 0.0f;
-    #pragma unroll
-                    for (int c = 0; c < 6; ++c)
-                        acc = fmaf(mb[90 + r * 6 + c], sv[(c / 2) * 5 + 3 + c % 2], acc);
-                    uv[(r / 2) * 5 + 3 + r % 2] = acc;
-                }
-                // odd-even: y 3..4, x 0..2
-    #pragma unroll
-                for (int r = 0; r < 6; ++r) {
-                    float acc = 0.0f;
-    #pragma unroll
-                    for (int c = 0; c < 6; ++c)
-                        acc = fmaf(mb[126 + r * 6 + c], sv[(3 + c / 3) * 5 + c % 3], acc);
-                    uv[(3 + r / 3) * 5 + r % 3] = acc;
-                }
-                // odd-odd: y 3..4, x 3..4
-    #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    float acc = 0.0f;
-    #pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        acc = fmaf(mb[162 + r * 4 + c], sv[(3 + c / 2) * 5 + 3 + c % 2], acc);
-                    uv[(3 + r / 2) * 5 + 3 + r % 2] = acc;
-                }
-                // back to nodes: transpose of the mirror transform, y then x
-    #pragma unroll
-                for (int i = 0; i < 5; ++i) {
-                    t[0 * 5 + i] = uv[0 * 5 + i] + uv[3 * 5 + i];
-                    t[4 * 5 + i] = uv[0 * 5 + i] - uv[3 * 5 + i];
-                    t[1 * 5 + i] = uv[1 * 5 + i] + uv[4 * 5 + i];
-                    t[3 * 5 + i] = uv[1 * 5 + i] - uv[4 * 5 + i];
-                    t[2 * 5 + i] = uv[2 * 5 + i];
-                }
-    #pragma unroll
-                for (int k = 0; k < 5; ++k) {
-                    const float *y = &t[k * 5];
-                    w[k * 5 + 0] = y[0] + y[3];
-                    w[k * 5 + 4] = y[0] - y[3];
-                    w[k * 5 + 1] = y[1] + y[4];
-                    w[k * 5 + 3] = y[1] - y[4];
-                    w[k * 5 + 2] = y[2];
-                }
-                w[25] = u25;
+                mirror(dz);
+                inverse_blocks(dz, false, w25);
+                mirror_back(dz, w);
                 cur = wy;
             }
             float v;
@@ -320,7 +347,7 @@ __global__ __launch_bounds__(kKrigCols) void k_kriging(const KrigArgs p)
                     fill_a = true;
                     acc = dot(cb);
                 }
-                v = kSeries ? zc + (w[25] + acc) : zc + (w[25] - acc);
+                v = kSeries ? zc + (w25 + acc) : zc + (w25 - acc);
             }
             p.dst[(int64_t)(row0 + r) * p.dnx + col0 + c] = v;
         }
@@ -329,6 +356,178 @@ __global__ __launch_bounds__(kKrigCols) void k_kriging(const KrigArgs p)
         walk(std::true_type{});
     else
         walk(std::false_type{});
+}
+
+// The same resample where the destination rows repeat at most two y offsets
+// (spacing equal to the source's, or half of it): the kriging weights
+//     lambda = A g + b,   z = z_c + sum_q lambda_q (z_q - z_c)
+// depend on a node's offsets in its window alone, so a thread walking down a
+// column keeps the weights of its last two y offsets in registers (K^-1 is
+// applied to the covariance terms once per offset instead of to every window),
+// and a node costs 25 multiply-adds.  The thread's 5 x 5 window slides in
+// registers (its rows take turns in the array, so nothing is moved); its next
+// row comes from the block's source rectangle in LDS (a load from memory inside
+// the row loop would wait for the loop's stores, which the same counter
+// covers), and lane r of a wave holds row r's offset.
+//
+// Bound by vector instruction issue (60 % of it at four waves per SIMD; half of
+// the rest is the start of each block: source rectangle, then weights).  2048^2
+// to 4096^2 on an MI355X: the other form 98.9 us, this one 54.9; 25 loads per
+// window instead of sliding, or the window moved in registers, 71; 32 rows per
+// block 59, 128 rows 83 (two waves per SIMD).  Error against 64 bits at ranges of
+// 0.5 to 9000 spacings: largest 0.8e-7 relative (the other form: 2.3e-7).
+constexpr int kPhaseRows = 64;     // destination rows per block, at most (a lane each)
+constexpr int kPhaseStage = 9984;  // source values staged in LDS, at most
+
+// Bilinear value of a node on its cell's corners.
+__device__ __forceinline__ float krig_bilinear(const KrigArgs &p, const Axis &ax, int row)
+{
+    const Axis ay = axis_of(p.dy0, p.ddy, row, p.sy0, p.sdy, p.sny);
+    const float *const r0 = p.src + (int64_t)ay.i0 * p.snx;
+    const float *const r1 = p.src + (int64_t)ay.i1 * p.snx;
+    const float q00 = r0[ax.i0], q10 = r0[ax.i1];
+    const float q01 = r1[ax.i0], q11 = r1[ax.i1];
+    const float top = q00 + ax.t * (q10 - q00);
+    const float bot = q01 + ax.t * (q11 - q01);
+    return top + ay.t * (bot - top);
+}
+
+template <bool kSeries>
+__global__ __launch_bounds__(kKrigCols, 4) void k_kriging_phase(const KrigArgs p)
+{
+    extern __shared__ float s_src[];  // the rectangle (launch_kriging sizes it)
+    const int row0 = blockIdx.y * p.rows;
+    const int nrow = min(p.rows, p.dny - row0);
+    // lane r of every wave holds row r's window start and y offset (bits)
+    int wy_l, dv_l;
+    {
+        const Axis a = axis_of(p.dy0, p.ddy, row0 + min((int)threadIdx.x & 63, nrow - 1), p.sy0,
+                               p.sdy, p.sny);
+        wy_l = window_start(a.u, p.sny);
+        dv_l = __float_as_int((float)(a.u - wy_l));
+    }
+    auto row_window = [&](int r) { return __builtin_amdgcn_readlane(wy_l, r); };
+    auto row_offset = [&](int r) { return __builtin_amdgcn_readlane(dv_l, r); };
+    const int col0 = blockIdx.x * kKrigCols, col = col0 + (int)threadIdx.x;
+    const int last = min(col0 + kKrigCols, p.dnx) - 1;
+    const Axis ax = axis_of(p.dx0, p.ddx, min(col, p.dnx - 1), p.sx0, p.sdx, p.snx);
+    const int wx = window_start(ax.u, p.snx);
+    const int il = window_start(axis_of(p.dx0, p.ddx, col0, p.sx0, p.sdx, p.snx).u, p.snx);
+    const int ih = window_start(axis_of(p.dx0, p.ddx, last, p.sx0, p.sdx, p.snx).u, p.snx) + 4;
+    const int jl = row_window(0), jh = row_window(nrow - 1) + 4;
+    const int sw = ih - il + 1;
+    stage_rect(p.src, p.snx, jl, il, sw, jh - jl + 1, s_src, kKrigCols);
+    __syncthreads();
+    // columns past the grid repeat the last one and store nothing (every lane
+    // stays active: the row table is read across lanes)
+    const bool on = col < p.dnx;
+    float ex2[5];
+    {
+        const float du = (float)(ax.u - wx);
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const float e = ((float)i - du) * p.fdx;
+            ex2[i] = e * e * p.c2;
+        }
+    }
+    // weights of y offset dv
+    auto weights = [&](float (&l)[25], float dv) {
+        float g[25];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            const float ey = ((float)k - dv) * p.fdy;
+            const float ey2 = ey * ey * p.c2;
+#pragma unroll
+            for (int i = 0; i < 5; ++i)
+                g[k * 5 + i] = one_minus_exp<kSeries>(__builtin_amdgcn_sqrtf(ex2[i] + ey2));
+        }
+        mirror(g);
+        float one;
+        inverse_blocks(g, true, one);
+        mirror_back(g, l);
+    };
+    const float *const src = s_src + (wx - il);
+    // Runs of rows that share two offsets.  Both weights are computed before
+    // the window is loaded, so that the registers for that are free by then;
+    // one run is the rule, edges have a few.
+    int r = 0;
+#pragma unroll 1
+    while (r < nrow) {
+        float la[25] = {}, lb[25] = {};
+        const int da = row_offset(r);
+        int rb = r + 1;
+        while (rb < nrow && row_offset(rb) == da)
+            ++rb;
+        const int db = row_offset(min(rb, nrow - 1));
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int q = 0; q < 25; ++q)
+                la[q] = lb[q];
+            if (h == 0 || db != da)
+                weights(lb, __int_as_float(h == 0 ? da : db));
+        }
+
+        int wy = row_window(r);
+        float z[5][5];
+        auto load_row = [&](int j, float (&to)[5]) {
+            const float *const row = src + (min(j, jh) - jl) * sw;
+#pragma unroll
+            for (int i = 0; i < 5; ++i)
+                to[i] = row[i];
+        };
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+            load_row(wy + k, z[k]);
+        // The rows of the window whose first source row is z[kFirst], then one
+        // source row down (into that row: the window turns in the array).
+        // Rows that share a window mostly have one offset each, so both values
+        // are computed together.  False after the run's last row.
+        auto window = [&](auto first) -> bool {
+            constexpr int kFirst = decltype(first)::value;
+            const float zc = z[(kFirst + 2) % 5][2];
+            float va = 0.0f, vb = 0.0f;
+            if (db != da) {
+#pragma unroll
+                for (int q = 0; q < 25; ++q) {
+                    const float d = z[(kFirst + q / 5) % 5][q % 5] - zc;
+                    va = fmaf(la[q], d, va);
+                    vb = fmaf(lb[q], d, vb);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < 25; ++q)
+                    vb = fmaf(lb[q], z[(kFirst + q / 5) % 5][q % 5] - zc, vb);
+            }
+#pragma unroll 1
+            for (; r < nrow && row_window(r) == wy; ++r) {
+                const int dv = row_offset(r);
+                if (dv != da && dv != db)
+                    return false;
+                float v = zc + (dv == db ? vb : va);
+                if (!isfinite(v)) {
+                    // a non-finite neighbour: bilinear on the node's cell corners
+                    float t = 0.0f;  // NaN with any non-finite value
+#pragma unroll
+                    for (int q = 0; q < 25; ++q)
+                        t = fmaf(z[q / 5][q % 5], 0.0f, t);
+                    if (t != 0.0f)
+                        v = krig_bilinear(p, ax, row0 + r);
+                }
+                if (on)
+                    __builtin_nontemporal_store(v, p.dst + (int64_t)(row0 + r) * p.dnx + col);
+            }
+            ++wy;
+            load_row(wy + 4, z[kFirst]);
+            return r < nrow;
+        };
+        while (window(std::integral_constant<int, 0>{}) &&
+               window(std::integral_constant<int, 1>{}) &&
+               window(std::integral_constant<int, 2>{}) &&
+               window(std::integral_constant<int, 3>{}) &&
+               window(std::integral_constant<int, 4>{})) {
+        }
+    }
 }
 
 // Inverse of the 26 x 26 kriging matrix for node spacing (dx, dy) and range a,
@@ -527,14 +726,39 @@ auv_status launch_kriging(const float *src, const auv_grid_desc &s, float *dst,
         return fail(AUV_ERR_INVALID, "singular kriging system for this spacing and range");
     if (!mirror_blocks(kinv, p.mb))
         return fail(AUV_ERR_INVALID, "kriging inverse lost its mirror symmetry (range far outside the node spacing)");
-    // more rows per block reuse more covariance terms, but a small grid needs
-    // the blocks: halve from kKrigRows (down to 8) while under 1024 blocks
+    // Destination rows at the source's spacing or half of it have one or two y
+    // offsets (and a few more at the edges): the form that keeps their weights.
+    // Elsewhere every row would compute weights of its own, which costs it as
+    // much as a window's product costs the other form, shared by its rows.
+    bool phase = std::fabs(d.dy - s.dy) <= 1e-9 * s.dy ||
+                 std::fabs(2.0 * d.dy - s.dy) <= 1e-9 * s.dy;
+    // more rows per block reuse more covariance terms or weights, but a small
+    // grid needs the blocks: halve (down to 8) while under 1024 blocks
     const int64_t ncb = (d.nx + kKrigCols - 1) / kKrigCols;
-    p.rows = kKrigRows;
+    p.rows = phase ? kPhaseRows : kKrigRows;
     while (p.rows > 8 && ncb * ((d.ny + p.rows - 1) / p.rows) < 1024)
         p.rows /= 2;
+    // and the block's source rectangle has to fit kPhaseStage values, which
+    // leave four blocks to a CU (two rows of slack for the rounding of the
+    // axis maps)
+    const double sw = std::min((double)s.nx, std::ceil((kKrigCols - 1) * d.dx / s.dx) + 7.0);
+    auto rect = [&](int rows) {
+        return sw * std::min((double)s.ny, std::ceil((rows - 1) * d.dy / s.dy) + 7.0);
+    };
+    while (phase && rect(p.rows) > kPhaseStage) {
+        if (p.rows > 8) {
+            p.rows /= 2;
+        } else {
+            phase = false;
+        }
+    }
+    const size_t lds = phase ? sizeof(float) * (size_t)rect(p.rows) : 0;
     const dim3 grid((unsigned)ncb, (unsigned)((d.ny + p.rows - 1) / p.rows));
-    if (series)
+    if (phase && series)
+        k_kriging_phase<true><<<grid, kKrigCols, lds, st>>>(p);
+    else if (phase)
+        k_kriging_phase<false><<<grid, kKrigCols, lds, st>>>(p);
+    else if (series)
         k_kriging<true><<<grid, kKrigCols, 0, st>>>(p);
     else
         k_kriging<false><<<grid, kKrigCols, 0, st>>>(p);
