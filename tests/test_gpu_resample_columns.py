@@ -1,5 +1,5 @@
-"""GPU parity of the Catmull-Rom resample's column form against the FP64 oracle
-where it can go wrong: sources of one and two nodes, destinations cut inside a
+"""GPU parity of the column form of the bilinear and Catmull-Rom resamples against
+the FP64 oracle where it can go wrong: sources of one and two nodes, destinations cut inside a
 wave and inside a block's rows, ratios whose tap rows slide, repeat or jump,
 source rectangles around and beyond the staged size, row lengths that are no
 multiple of four, holes of NaN and infinities.
@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
 REL = 1e-5
 
 
+@pytest.mark.parametrize("method", ["bilinear", "bicubic"])
 @pytest.mark.parametrize("snx,sny,dnx,dny,shift,hole", [
     (1, 1, 3, 5, 0.0, 0.0),
     (2, 300, 255, 33, 0.0, 0.0),
@@ -26,7 +27,7 @@ REL = 1e-5
     (3000, 40, 260, 39, 0.0, 0.001),     # beyond the staged size
     (500, 3, 1030, 7, 0.0, 0.01),
 ])
-def test_bicubic_columns(orc, snx, sny, dnx, dny, shift, hole):
+def test_resample_columns(orc, method, snx, sny, dnx, dny, shift, hole):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2505_22675_amd as ag
@@ -38,10 +39,11 @@ def test_bicubic_columns(orc, snx, sny, dnx, dny, shift, hole):
     z[u < hole] = np.nan
     z[u < hole / 4] = np.inf
     dst = torch.full((dny, dnx), -7.0, dtype=torch.float32, device="cuda")
-    ag.auv_resample_bicubic(torch.from_numpy(z).cuda(), g, dst, d)
+    getattr(ag, f"auv_resample_{method}")(torch.from_numpy(z).cuda(), g, dst, d)
     torch.cuda.synchronize()
-    want = orc.bicubic(orc.Grid(g.x0, g.y0, g.dx, g.dy, snx, sny), z.astype(np.float64),
-                       orc.Grid(d.x0, d.y0, d.dx, d.dy, dnx, dny))
+    want = getattr(orc, method)(orc.Grid(g.x0, g.y0, g.dx, g.dy, snx, sny),
+                                z.astype(np.float64),
+                                orc.Grid(d.x0, d.y0, d.dx, d.dy, dnx, dny))
     got = dst.cpu().numpy().astype(np.float64)
     assert np.array_equal(np.isfinite(got), np.isfinite(want))
     ok = np.isfinite(want)
