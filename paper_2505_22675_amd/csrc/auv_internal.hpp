@@ -100,7 +100,7 @@ struct BinWorkspace {
     int32_t *big_list;    // [nb] bins too long for one thread
     int32_t *row_count;   // [nby] soundings per bin row (row path)
     int32_t *row_start;   // [nby + 1]
-    int32_t *rowid;       // [n] bin row per input sounding (or -1)
+    int32_t *rowid;       // [n] bin row | column << 16 per input sounding (or -1)
     unsigned long long *keys;  // [n] (bin column << 32 | original index)
     unsigned long long *keys2; // [n] scratch for the per-row sort
     int32_t *drops;            // per-block dropped-sounding counters
@@ -127,7 +127,7 @@ struct RowItem {
     // optional (serving): lattice box X min, Y min, X max, Y max of the
     // binned soundings, widened atomically from a caller-seeded empty box
     int32_t *bbox;
-    int32_t *row_count, *row_start, *rowid, *pos, *colkey, *drops, *cell_start;
+    int32_t *row_count, *row_start, *rowcol, *pos, *drops, *cell_start;
     int4 *rec;
     unsigned long long *keys, *keys2, *stats;
     SoA o;
@@ -165,15 +165,21 @@ RowItem make_row_item(const auv_grid *g, const BinGeom &geom, const double *x,
                       const double *y, const double *z, int64_t n, const BinWorkspace &w);
 int32_t row_hist_blocks(int64_t n);
 int32_t row_scatter_blocks(int64_t n);
-// max_nbx / max_nby: the largest bin domain among the items (sizes the LDS);
-// keys_per_row: the largest mean of input soundings per bin row among the
-// items (picks the sort's LDS key area; longer rows stay correct, on slower
-// paths).
+// Rows by the size of the sort's LDS key area (its class, from the mean of
+// input soundings per bin row; longer rows stay correct, on slower paths): the
+// items are ordered by class, so each class is a range of sort blocks.
+constexpr int kRowSortClasses = 3;
+struct RowSortClass {
+    int32_t block0 = 0, block1 = 0;
+    int32_t max_nbx = 0;  // most bin columns of its items (sizes the LDS)
+};
+int row_sort_class(double keys_per_row);
+// max_nbx / max_nby: the largest bin domain among the items (sizes the LDS).
 auv_status launch_binning_batch(const RowItem *d_items, const int32_t *d_hist_off,
                                 const int32_t *d_scatter_off, const int32_t *d_sort_off,
                                 int32_t count, int32_t hist_blocks, int32_t scatter_blocks,
-                                int32_t sort_blocks, int32_t max_nbx, int32_t max_nby,
-                                double keys_per_row, hipStream_t st);
+                                const RowSortClass (&classes)[kRowSortClasses],
+                                int32_t max_nbx, int32_t max_nby, hipStream_t st);
 
 // The work of auv_bin_points into a caller-provided handle (no allocation).
 auv_status bin_into(const auv_grid *grid, const double *x, const double *y, const double *z,

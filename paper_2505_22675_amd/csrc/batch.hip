@@ -271,14 +271,13 @@ struct auv_batch {
     std::vector<auv::IdwItem> idw;
     std::vector<int32_t> offs;  // hist, scatter, sort offsets
     std::vector<int2> work;
-    int32_t hist_blocks = 0, scatter_blocks = 0, sort_blocks = 0, nrow_items = 0;
+    int32_t hist_blocks = 0, scatter_blocks = 0, nrow_items = 0;
+    auv::RowSortClass sort_class[auv::kRowSortClasses];
     int32_t work_off[auv::kForms + 1] = {0, 0, 0, 0};  // each form's units in `work`
     bool any_general = false;  // a sparse item with a general power
     int32_t max_nbx = 0, max_nby = 0;  // largest bin domain of the row-binned items
-    double keys_per_row = 0.0;          // largest mean of soundings per bin row
     hipStream_t cap_stream2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-    std::vector<int32_t> row_items;  // items binned by the batched row path
     // graph
     void *bound_ws = nullptr;
     hipStream_t cap_stream = nullptr;
@@ -433,9 +432,7 @@ auv_status build_tables(auv_batch *b, char *ws)
     const int count = (int)b->items.size();
     b->rows.assign(count, RowItem{});
     b->max_nbx = b->max_nby = 0;
-    b->keys_per_row = 0.0;
     b->idw.assign(count, IdwItem{});
-    b->row_items.clear();
     std::vector<int32_t> hist(1, 0), scat(1, 0), sort(1, 0);
     std::vector<double> tile_cost(count, 0.0);
     for (int i = 0; i < count; ++i) {
@@ -444,18 +441,6 @@ auv_status build_tables(auv_batch *b, char *ws)
         auv_bin_view bv;
         IdwArgs a;
         item_views(b, i, ws, b->geom[i], b->algo[i], &w, &bv, &a, b->tile[i]);
-        if (row_path_ok(b->geom[i])) {
-            b->rows[b->row_items.size()] =
-                make_row_item(&b->grids[i], b->geom[i], it.x, it.y, it.z, it.n, w);
-            b->row_items.push_back(i);
-            hist.push_back(hist.back() + row_hist_blocks(it.n));
-            scat.push_back(scat.back() + row_scatter_blocks(it.n));
-            sort.push_back(sort.back() + b->geom[i].nby);
-            b->max_nbx = std::max(b->max_nbx, b->geom[i].nbx);
-            b->max_nby = std::max(b->max_nby, b->geom[i].nby);
-            b->keys_per_row =
-                std::max(b->keys_per_row, (double)it.n / std::max(1, b->geom[i].nby));
-        }
         IdwItem &d = b->idw[i];
         const bool ok = make_idw_item(it, bv, a, b->algo[i], &d) && row_path_ok(b->geom[i]);
         b->covered[i] = ok ? 1 : 0;
@@ -474,10 +459,32 @@ auv_status build_tables(auv_batch *b, char *ws)
             tile_cost[i] = 20.0 + rho * bw * bh;
         }
     }
-    b->nrow_items = (int32_t)b->row_items.size();
+    // row-binned items by the class of their rows' sort
+    b->nrow_items = 0;
+    for (int sc = 0; sc < kRowSortClasses; ++sc) {
+        RowSortClass &c = b->sort_class[sc];
+        c = RowSortClass{};
+        c.block0 = sort.back();
+        for (int i = 0; i < count; ++i) {
+            const auv_batch_item &it = b->items[i];
+            const BinGeom &g = b->geom[i];
+            if (!row_path_ok(g) || row_sort_class((double)it.n / std::max(1, g.nby)) != sc)
+                continue;
+            BinWorkspace w;
+            bin_workspace_layout(it.n, g, ws + b->slice_off[i], &w);
+            b->rows[b->nrow_items++] =
+                make_row_item(&b->grids[i], g, it.x, it.y, it.z, it.n, w);
+            hist.push_back(hist.back() + row_hist_blocks(it.n));
+            scat.push_back(scat.back() + row_scatter_blocks(it.n));
+            sort.push_back(sort.back() + g.nby);
+            c.max_nbx = std::max(c.max_nbx, g.nbx);
+            b->max_nbx = std::max(b->max_nbx, g.nbx);
+            b->max_nby = std::max(b->max_nby, g.nby);
+        }
+        c.block1 = sort.back();
+    }
     b->hist_blocks = hist.back();
     b->scatter_blocks = scat.back();
-    b->sort_blocks = sort.back();
     // units by form, items with the costliest tiles first (a wave takes a tile
     // alone, so a long tile late in the launch would end it late)
     std::vector<int> order(count);
@@ -541,8 +548,8 @@ auv_status enqueue_batched(auv_batch *b, char *ws, hipStream_t st)
     const int count = (int)b->items.size();
     const int nr = b->nrow_items;
     AUV_TRY_S(launch_binning_batch(t.rows, t.offs, t.offs + (nr + 1), t.offs + 2 * (nr + 1), nr,
-                                   b->hist_blocks, b->scatter_blocks, b->sort_blocks,
-                                   b->max_nbx, b->max_nby, b->keys_per_row, st));
+                                   b->hist_blocks, b->scatter_blocks, b->sort_class, b->max_nbx,
+                                   b->max_nby, st));
     for (int i = 0; i < count; ++i) {
         if (row_path_ok(b->geom[i]))
             continue;

@@ -48,8 +48,9 @@ __device__ inline int wave_inclusive_scan(int v)
     return v;
 }
 
-// Exclusive scan of one value per thread across a 256-thread block; also
-// returns the block total.  Uses `lds` (4 ints).
+// Exclusive scan of one value per thread across a block of kT threads; also
+// returns the block total.  Uses `lds` (kT / 64 ints).
+template <int kT = kThreads>
 __device__ inline int block_exclusive_scan(int v, int *lds, int *total)
 {
     const int wave = threadIdx.x >> 6, lane = lane_id();
@@ -59,7 +60,7 @@ __device__ inline int block_exclusive_scan(int v, int *lds, int *total)
     __syncthreads();
     int base = 0, sum = 0;
 #pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) {
+    for (int w = 0; w < kT / 64; ++w) {
         int t = lds[w];
         base += (w < wave) ? t : 0;
         sum += t;
@@ -316,12 +317,12 @@ __global__ __launch_bounds__(kThreads) void k_stabilise_big(
 // LDS is sized per launch from the bin domain (rows, columns), so small
 // domains keep many blocks resident.
 
-constexpr int kRowChunk = 1024;          // soundings per block in k_row_hist
-constexpr int kRowPerThread = kRowChunk / kThreads;
-constexpr int kMaxRowsLds = 8192;        // bin rows in the LDS histogram
+constexpr int kRowPerThread = 4;         // soundings per thread in k_row_hist
+constexpr int kMaxRowsLds = 8192;        // bin rows in the LDS histogram (15 bits of rowcol)
 constexpr int kScatterPer = 4;           // soundings per thread in k_row_scatter
 constexpr int kRunsMax = 8;              // row runs per wave for the grouped reservation
 
+template <int kT>
 __device__ void row_hist_block(const RowItem &it, int blk, int *s_cnt)
 {
     typedef int v4i __attribute__((ext_vector_type(4)));
@@ -332,22 +333,22 @@ __device__ void row_hist_block(const RowItem &it, int blk, int *s_cnt)
     const double x0 = it.x0, y0 = it.y0, lo = it.lo, hix = it.hix, hiy = it.hiy;
     const int32_t s = it.s, hB = it.hB, nby = it.nby;
     const auto row_count = gmem(it.row_count);
-    const auto rowid = gmem(it.rowid);
+    const auto rowcol = gmem(it.rowcol);
     const auto pos = gmem(it.pos);
-    const auto colkey = gmem(it.colkey);
     const auto rec = gmem(reinterpret_cast<v4i *>(it.rec));
     const auto drops = gmem(it.drops);
-    for (int r = threadIdx.x; r < nby; r += kThreads)
+    for (int r = threadIdx.x; r < nby; r += kT)
         s_cnt[r] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blk * kRowChunk + threadIdx.x;
-    int row[kRowPerThread], lr[kRowPerThread];
+    const int64_t base = (int64_t)blk * (kT * kRowPerThread) + threadIdx.x;
+    int row[kRowPerThread], col[kRowPerThread], lr[kRowPerThread];
     int bad = 0, out = 0;
     int blx = INT_MAX, bly = INT_MAX, bhx = INT_MIN, bhy = INT_MIN;  // box of the binned
 #pragma unroll
     for (int j = 0; j < kRowPerThread; ++j) {
-        const int64_t i = base + (int64_t)j * kThreads;
+        const int64_t i = base + (int64_t)j * kT;
         row[j] = -1;
+        col[j] = 0;
         lr[j] = 0;
         if (i < n) {
             const double xi = x[i], yi = y[i], zi = z[i];
@@ -363,7 +364,7 @@ __device__ void row_hist_block(const RowItem &it, int blk, int *s_cnt)
                     const int qy = (int)rint((ty - ry) * 32768.0);
                     const uint32_t rr = ((uint32_t)qx & 0xffffu) | ((uint32_t)qy << 16);
                     rec[i] = v4i{X, Y, (int)rr, __float_as_int((float)zi)};
-                    colkey[i] = (X + hB) >> s;
+                    col[j] = (X + hB) >> s;
                     row[j] = (Y + hB) >> s;
                     blx = min(blx, X);
                     bhx = max(bhx, X);
@@ -404,7 +405,7 @@ __device__ void row_hist_block(const RowItem &it, int blk, int *s_cnt)
         }
     }
     __syncthreads();
-    for (int r = threadIdx.x; r < nby; r += kThreads) {
+    for (int r = threadIdx.x; r < nby; r += kT) {
         const int c = s_cnt[r];
         if (c)
             s_cnt[r] = __hip_atomic_fetch_add(&row_count[r], c, __ATOMIC_RELAXED,
@@ -413,9 +414,9 @@ __device__ void row_hist_block(const RowItem &it, int blk, int *s_cnt)
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kRowPerThread; ++j) {
-        const int64_t i = base + (int64_t)j * kThreads;
+        const int64_t i = base + (int64_t)j * kT;
         if (i < n) {
-            rowid[i] = row[j];
+            rowcol[i] = row[j] >= 0 ? row[j] | (col[j] << 16) : -1;
             pos[i] = row[j] >= 0 ? s_cnt[row[j]] + lr[j] : 0;
         }
     }
@@ -438,9 +439,9 @@ __device__ void row_hist_block(const RowItem &it, int blk, int *s_cnt)
     // one address per wave would serialise at the memory side)
     int tb, tob;
     {
-        __shared__ int lds_b[kThreads / 64];
-        block_exclusive_scan(bad, lds_b, &tb);
-        block_exclusive_scan(out, lds_b, &tob);
+        __shared__ int lds_b[kT / 64];
+        block_exclusive_scan<kT>(bad, lds_b, &tb);
+        block_exclusive_scan<kT>(out, lds_b, &tob);
     }
     if (threadIdx.x == 0) {
         drops[2 * blk] = tb;
@@ -494,20 +495,23 @@ __device__ void row_scatter_block(const RowItem &it, int blk, int *s_rs, int *ld
             it.stats[0] = (unsigned long long)carry;
         }
     }
-    const auto rowid = gmem(it.rowid);
+    const auto rowcol = gmem(it.rowcol);
     const auto pos = gmem(it.pos);
-    const auto colkey = gmem(it.colkey);
     const auto keys = gmem(it.keys);
     const int64_t base = (int64_t)blk * (kThreads * kScatterPer) + threadIdx.x;
+    int rc[kScatterPer], at[kScatterPer];
 #pragma unroll
     for (int j = 0; j < kScatterPer; ++j) {
         const int64_t i = base + (int64_t)j * kThreads;
-        if (i < it.n) {
-            const int r = rowid[i];
-            if (r >= 0)
-                keys[s_rs[r] + pos[i]] =
-                    ((unsigned long long)(uint32_t)colkey[i] << 32) | (uint32_t)i;
-        }
+        rc[j] = i < it.n ? rowcol[i] : -1;
+        at[j] = i < it.n ? pos[i] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < kScatterPer; ++j) {
+        const int64_t i = base + (int64_t)j * kThreads;
+        if (rc[j] >= 0)
+            keys[s_rs[rc[j] & 0xffff] + at[j]] =
+                ((unsigned long long)(uint32_t)(rc[j] >> 16) << 32) | (uint32_t)i;
     }
 }
 
@@ -515,7 +519,7 @@ __device__ void row_scatter_block(const RowItem &it, int blk, int *s_rs, int *ld
 // padded with +inf up to a power of two, and pairs whose upper element lies in
 // the padding are skipped (the mirrored first step of each merge keeps every
 // comparison ascending, so padding never moves).  Whole block, any memory.
-template <class P>
+template <int kT, class P>
 __device__ void block_bitonic_sort(P a, int n)
 {
     using T = unsigned long long;
@@ -525,7 +529,7 @@ __device__ void block_bitonic_sort(P a, int n)
     const int pairs = npow >> 1;
     for (int size = 2; size <= npow; size <<= 1) {
         const int half = size >> 1;
-        for (int t = threadIdx.x; t < pairs; t += kThreads) {
+        for (int t = threadIdx.x; t < pairs; t += kT) {
             const int blk = t / half, off = t - blk * half;
             const int i = blk * size + off, j = blk * size + size - 1 - off;
             if (j < n) {
@@ -539,7 +543,7 @@ __device__ void block_bitonic_sort(P a, int n)
         __threadfence_block();
         __syncthreads();
         for (int stride = size >> 2; stride > 0; stride >>= 1) {
-            for (int t = threadIdx.x; t < pairs; t += kThreads) {
+            for (int t = threadIdx.x; t < pairs; t += kT) {
                 const int blk = t / stride, off = t - blk * stride;
                 const int i = blk * 2 * stride + off, j = i + stride;
                 if (j < n) {
@@ -561,55 +565,76 @@ __device__ void block_bitonic_sort(P a, int n)
 // bin, members are ordered by original index: by ranking (rank = number of
 // members with a smaller index) when every bin of the row is small, else by
 // a bitonic sort of the row's (column, index) keys (in LDS when they fit,
-// otherwise in place in the key array).  Rows of up to kRowLds keys rank in
-// LDS: the keys are re-read (coalesced) from global memory in each pass and
-// only the indices are scattered into their bins in LDS; longer rows rank
-// through tmp_keys.  (Swath data gives lumpy rows: a ping line spans a bin
+// otherwise in place in the key array).  Rows that fit the block's registers
+// (kStage keys) are read once and their records gathered at once, before the
+// histogram, whose atomics return the arrival slots; rows of up to kRank keys
+// rank in LDS too, their keys re-read (coalesced) in each pass and only the
+// indices scattered into their bins; longer rows rank through tmp_keys.  A small
+// call is one chain of waits per row: reading the keys once, gathering early and
+// four members per step of the ranking took 33 rows of 600 keys 11.8 -> 7.1 us,
+// 377 of 1300 16.8 -> 13.8, 1026 of 2000 21.0 -> 19.3.  (Swath data gives lumpy rows: a ping line spans a bin
 // row, so a row holds zero, one or two pings' worth of soundings.)
 constexpr int kColsLds = 8192;
 constexpr int kSmallRank = 64;     // largest bin ranked member by member
 constexpr int kRowU = 8;           // keys per thread per pass: loads kept in flight
 // The sort's LDS key area holds kKA u64 keys: rows of up to kKA keys are
 // bitonic-sorted there, rows of up to 2 kKA keys rank there (as u32
-// indices), and rows of up to kThreads * kSU keys are ranked in registers
+// indices), and rows of up to kT * kSU keys are ranked in registers
 // (kSU per thread) and written out through two LDS arrays of that length
 // carved from it.  Longer rows take the global-memory paths.  Three sizes:
 // a smaller area and fewer staged keys per thread let more blocks share a
 // CU (registers and LDS), for rows that are short on average.
-template <int kKA, int kSU>
+template <int kT, int kKA, int kSU>
 struct SortCfg {
-    static constexpr int kBitonic = kKA, kRank = 2 * kKA, kStage = kThreads * kSU;
-    static_assert(2 * kThreads * kSU * sizeof(int32_t) <= kKA * sizeof(unsigned long long),
+    static constexpr int kBitonic = kKA, kRank = 2 * kKA, kStage = kT * kSU;
+    static_assert(2 * kT * kSU * sizeof(int32_t) <= kKA * sizeof(unsigned long long),
                   "row staging does not fit the key area");
-    static_assert(kThreads * kSU <= 2 * kKA, "staged rows must take the LDS ranking");
+    static_assert(kT * kSU <= 2 * kKA, "staged rows must take the LDS ranking");
 };
 
-// for (k = threadIdx.x; k < n; k += kThreads) f(k, keys[r0 + k]), with kRowU
+// for (k = threadIdx.x; k < n; k += kT) f(k, keys[r0 + k]), with kRowU
 // key loads issued before any is used
-template <class KP, class F>
+template <int kT, class KP, class F>
 __device__ inline void for_row_keys(KP keys, int r0, int n, F f)
 {
-    for (int k0 = threadIdx.x; k0 < n; k0 += kThreads * kRowU) {
+    for (int k0 = threadIdx.x; k0 < n; k0 += kT * kRowU) {
         unsigned long long kk[kRowU];
 #pragma unroll
         for (int j = 0; j < kRowU; ++j) {
-            const int k = k0 + j * kThreads;
+            const int k = k0 + j * kT;
             kk[j] = k < n ? keys[r0 + k] : 0ull;
         }
 #pragma unroll
         for (int j = 0; j < kRowU; ++j) {
-            const int k = k0 + j * kThreads;
+            const int k = k0 + j * kT;
             if (k < n)
                 f(k, kk[j]);
         }
     }
 }
 
-template <int kKA, int kSU>
+// Members of a bin (s_i[b0, b1)) below v, four reads in flight (the reads past
+// b1 stay inside the LDS block: the columns' starts follow the key area).
+__device__ inline int rank_of(const uint32_t *s_i, int b0, int b1, uint32_t v)
+{
+    int rank = 0;
+    for (int q = b0; q < b1; q += 4) {
+        uint32_t m[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            m[u] = s_i[q + u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            rank += (q + u < b1) & (m[u] < v) ? 1 : 0;
+    }
+    return rank;
+}
+
+template <int kT, int kKA, int kSU>
 __device__ void row_sort_block(const RowItem &it, int row, int *s_h,
                                unsigned long long *s_k, int *lds)
 {
-    using C = SortCfg<kKA, kSU>;
+    using C = SortCfg<kT, kKA, kSU>;
     typedef int v4i __attribute__((ext_vector_type(4)));
     const auto keys = gmem(it.keys);
     const auto row_start = gmem(it.row_start);
@@ -632,12 +657,36 @@ __device__ void row_sort_block(const RowItem &it, int row, int *s_h,
         oIdx[pos] = orig;
     };
     const int r0 = row_start[row], n = row_start[row + 1] - r0;
-    for (int bx = threadIdx.x; bx < nbx; bx += kThreads)
+    // rows of up to kStage keys: read once, kSU per thread, with their records
+    // gathered meanwhile; the histogram's return value is the arrival slot
+    const bool held = n <= C::kStage;
+    uint32_t ix[kSU];
+    int pos[kSU], slot[kSU];
+    int4 rr[kSU];
+    if (held) {
+#pragma unroll
+        for (int j = 0; j < kSU; ++j) {
+            const int k = (int)threadIdx.x + j * kT;
+            const unsigned long long key = k < n ? keys[r0 + k] : 0ull;
+            ix[j] = (uint32_t)key;
+            pos[j] = k < n ? (int)(key >> 32) : -1;  // bin column until ranked
+        }
+    }
+    for (int bx = threadIdx.x; bx < nbx; bx += kT)
         s_h[bx] = 0;
     __syncthreads();
-    for_row_keys(keys, r0, n, [&](int, unsigned long long key) {
-        atomicAdd(&s_h[(int)(key >> 32)], 1);
-    });
+    if (held) {
+#pragma unroll
+        for (int j = 0; j < kSU; ++j)
+            if (pos[j] >= 0) {
+                rr[j] = load_rec(ix[j]);
+                slot[j] = atomicAdd(&s_h[pos[j]], 1);
+            }
+    } else {
+        for_row_keys<kT>(keys, r0, n, [&](int, unsigned long long key) {
+            atomicAdd(&s_h[(int)(key >> 32)], 1);
+        });
+    }
     __syncthreads();
     const auto cs = cell_start + (int64_t)row * nbx;
     // bin starts within the row: each thread sums a run of consecutive
@@ -645,7 +694,7 @@ __device__ void row_sort_block(const RowItem &it, int row, int *s_h,
     // run's starts into s_h; cell_start is written from s_h, coalesced
     int big = 0;
     {
-        const int per = (nbx + kThreads - 1) / kThreads;
+        const int per = (nbx + kT - 1) / kT;
         const int c0 = min(nbx, (int)threadIdx.x * per), c1 = min(nbx, c0 + per);
         int sum = 0;
         for (int bx = c0; bx < c1; ++bx) {
@@ -654,130 +703,116 @@ __device__ void row_sort_block(const RowItem &it, int row, int *s_h,
             big |= v > kSmallRank ? 1 : 0;
         }
         int total;
-        int run = block_exclusive_scan(sum, lds, &total);
+        int run = block_exclusive_scan<kT>(sum, lds, &total);
         for (int bx = c0; bx < c1; ++bx) {
             const int v = s_h[bx];
             s_h[bx] = run;
             run += v;
         }
+        if (threadIdx.x == 0)
+            s_h[nbx] = n;
         __syncthreads();
-        for (int bx = threadIdx.x; bx < nbx; bx += kThreads)
+        for (int bx = threadIdx.x; bx < nbx; bx += kT)
             cs[bx] = r0 + s_h[bx];
     }
     if (row == nby - 1 && threadIdx.x == 0)
         cell_start[(int64_t)nby * nbx] = row_start[nby];
     if (__syncthreads_or(big)) {
         if (n <= C::kBitonic) {
-            for (int k = threadIdx.x; k < n; k += kThreads)
+            for (int k = threadIdx.x; k < n; k += kT)
                 s_k[k] = keys[r0 + k];
             __syncthreads();
-            block_bitonic_sort(s_k, n);
-            for (int k = threadIdx.x; k < n; k += kThreads)
+            block_bitonic_sort<kT>(s_k, n);
+            for (int k = threadIdx.x; k < n; k += kT)
                 emit_g(r0 + k, (int)(uint32_t)(s_k[k] & 0xffffffffull));
         } else {
             const auto a = keys + r0;
-            block_bitonic_sort(a, n);
-            for (int k = threadIdx.x; k < n; k += kThreads)
+            block_bitonic_sort<kT>(a, n);
+            for (int k = threadIdx.x; k < n; k += kT)
                 emit_g(r0 + k, (int)(uint32_t)(a[k] & 0xffffffffull));
         }
+        return;
+    }
+    if (held) {
+        // the indices go to their bins in LDS (unordered inside a bin), each is
+        // ranked there, then the records are placed at their sorted slots in
+        // LDS (the index list is dead by then) and written out contiguously,
+        // two arrays at a time
+        uint32_t *s_i = reinterpret_cast<uint32_t *>(s_k);
+#pragma unroll
+        for (int j = 0; j < kSU; ++j)
+            if (pos[j] >= 0)
+                s_i[s_h[pos[j]] + slot[j]] = ix[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kSU; ++j)
+            if (pos[j] >= 0) {
+                const int b0 = s_h[pos[j]], b1 = s_h[pos[j] + 1];
+                pos[j] = b0 + rank_of(s_i, b0, b1, ix[j]);
+            }
+        int32_t *s_a = reinterpret_cast<int32_t *>(s_k);
+        int32_t *s_b = s_a + kT * kSU;
+        __syncthreads();  // every rank is read: the index list is free
+#pragma unroll
+        for (int j = 0; j < kSU; ++j)
+            if (pos[j] >= 0) {
+                s_a[pos[j]] = rr[j].x;
+                s_b[pos[j]] = rr[j].y;
+            }
+        __syncthreads();
+        for (int k = threadIdx.x; k < n; k += kT) {
+            oX[r0 + k] = s_a[k];
+            oY[r0 + k] = s_b[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kSU; ++j)
+            if (pos[j] >= 0) {
+                s_a[pos[j]] = rr[j].z;
+                s_b[pos[j]] = rr[j].w;
+            }
+        __syncthreads();
+        for (int k = threadIdx.x; k < n; k += kT) {
+            oRes[r0 + k] = (uint32_t)s_a[k];
+            oZ[r0 + k] = __int_as_float(s_b[k]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kSU; ++j)
+            if (pos[j] >= 0)
+                s_a[pos[j]] = (int)ix[j];
+        __syncthreads();
+        for (int k = threadIdx.x; k < n; k += kT)
+            oIdx[r0 + k] = s_a[k];
         return;
     }
     if (n <= C::kRank) {
         // scatter the indices into their bins (unordered inside a bin);
         // afterwards s_h[bx] is the end of bin bx, i.e. the start of bx + 1
         uint32_t *s_i = reinterpret_cast<uint32_t *>(s_k);
-        for_row_keys(keys, r0, n, [&](int, unsigned long long key) {
+        for_row_keys<kT>(keys, r0, n, [&](int, unsigned long long key) {
             const int p = atomicAdd(&s_h[(int)(key >> 32)], 1);
             s_i[p] = (uint32_t)key;
         });
         __syncthreads();
-        if (n <= C::kStage) {
-            // one pass: ranks and gathers in registers, then the records are
-            // placed at their sorted slots in LDS (the index list is dead by
-            // then) and written out contiguously, two arrays at a time
-            const int k0 = threadIdx.x;
-            uint32_t ix[kSU];
-            int pos[kSU];
-            int4 rr[kSU];
-#pragma unroll
-            for (int j = 0; j < kSU; ++j) {
-                const int k = k0 + j * kThreads;
-                const unsigned long long key = k < n ? keys[r0 + k] : 0ull;
-                ix[j] = (uint32_t)key;
-                pos[j] = k < n ? (int)(key >> 32) : -1;  // bin column until ranked
-            }
-#pragma unroll
-            for (int j = 0; j < kSU; ++j) {
-                if (pos[j] >= 0) {
-                    const int bx = pos[j];
-                    const int b0 = bx == 0 ? 0 : s_h[bx - 1], b1 = s_h[bx];
-                    int rank = 0;
-                    for (int q = b0; q < b1; ++q)
-                        rank += s_i[q] < ix[j] ? 1 : 0;
-                    pos[j] = b0 + rank;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < kSU; ++j)
-                if (pos[j] >= 0)
-                    rr[j] = load_rec(ix[j]);
-            int32_t *s_a = reinterpret_cast<int32_t *>(s_k);
-            int32_t *s_b = s_a + kThreads * kSU;
-            __syncthreads();  // every rank is read: the index list is free
-#pragma unroll
-            for (int j = 0; j < kSU; ++j)
-                if (pos[j] >= 0) {
-                    s_a[pos[j]] = rr[j].x;
-                    s_b[pos[j]] = rr[j].y;
-                }
-            __syncthreads();
-            for (int k = threadIdx.x; k < n; k += kThreads) {
-                oX[r0 + k] = s_a[k];
-                oY[r0 + k] = s_b[k];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < kSU; ++j)
-                if (pos[j] >= 0) {
-                    s_a[pos[j]] = rr[j].z;
-                    s_b[pos[j]] = rr[j].w;
-                }
-            __syncthreads();
-            for (int k = threadIdx.x; k < n; k += kThreads) {
-                oRes[r0 + k] = (uint32_t)s_a[k];
-                oZ[r0 + k] = __int_as_float(s_b[k]);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < kSU; ++j)
-                if (pos[j] >= 0)
-                    s_a[pos[j]] = (int)ix[j];
-            __syncthreads();
-            for (int k = threadIdx.x; k < n; k += kThreads)
-                oIdx[r0 + k] = s_a[k];
-            return;
-        }
         // ranks first (LDS), then the kRowU record gathers in flight together
-        for (int k0 = threadIdx.x; k0 < n; k0 += kThreads * kRowU) {
+        for (int k0 = threadIdx.x; k0 < n; k0 += kT * kRowU) {
             unsigned long long kk[kRowU];
             int pos[kRowU];
             int4 rr[kRowU];
 #pragma unroll
             for (int j = 0; j < kRowU; ++j) {
-                const int k = k0 + j * kThreads;
+                const int k = k0 + j * kT;
                 kk[j] = k < n ? keys[r0 + k] : 0ull;
             }
 #pragma unroll
             for (int j = 0; j < kRowU; ++j) {
                 pos[j] = -1;
-                if (k0 + j * kThreads < n) {
+                if (k0 + j * kT < n) {
                     const int bx = (int)(kk[j] >> 32);
                     const uint32_t v = (uint32_t)kk[j];
                     const int b0 = bx == 0 ? 0 : s_h[bx - 1], b1 = s_h[bx];
-                    int rank = 0;
-                    for (int q = b0; q < b1; ++q)
-                        rank += s_i[q] < v ? 1 : 0;
-                    pos[j] = r0 + b0 + rank;
+                    pos[j] = r0 + b0 + rank_of(s_i, b0, b1, v);
                 }
             }
 #pragma unroll
@@ -797,7 +832,7 @@ __device__ void row_sort_block(const RowItem &it, int row, int *s_h,
         return;
     }
     const auto tmp_keys = gmem(it.keys2);
-    for (int k = threadIdx.x; k < n; k += kThreads) {
+    for (int k = threadIdx.x; k < n; k += kT) {
         const unsigned long long key = keys[r0 + k];
         const int p = atomicAdd(&s_h[(int)(key >> 32)], 1);
         tmp_keys[r0 + p] = key;
@@ -805,7 +840,7 @@ __device__ void row_sort_block(const RowItem &it, int row, int *s_h,
     __threadfence_block();
     __syncthreads();
     // one thread per sounding: its rank among its bin's members
-    for (int p = threadIdx.x; p < n; p += kThreads) {
+    for (int p = threadIdx.x; p < n; p += kT) {
         const unsigned long long key = tmp_keys[r0 + p];
         const int bx = (int)(key >> 32);
         const int b0 = bx == 0 ? 0 : s_h[bx - 1], b1 = s_h[bx];
@@ -821,7 +856,7 @@ inline size_t row_hist_lds(int nby) { return sizeof(int) * (size_t)nby; }
 inline size_t row_scatter_lds(int nby) { return sizeof(int) * (size_t)nby; }
 inline size_t row_sort_lds(int ka, int nbx)
 {
-    return sizeof(unsigned long long) * (size_t)ka + sizeof(int) * (size_t)nbx;
+    return sizeof(unsigned long long) * (size_t)ka + sizeof(int) * (size_t)(nbx + 1);
 }
 
 // Key-area configuration of the sort for rows averaging `keys_per_row`
@@ -832,6 +867,21 @@ inline int sort_config(double keys_per_row)
 }
 inline int sort_config_ka(int c) { return c == 0 ? 1024 : c == 1 ? 2048 : 4096; }
 
+// Rows sorted by 512 threads each: up to about two rows per CU, where a row's chain of
+// waits is the time (33 rows of 600 keys: 256 threads 8.6 us, 512 7.1, 1024 7.1;
+// 377 rows of 1300: 15.0, 13.8, 18.8); beyond that 256 threads leave more rows in
+// flight (1026 rows of 2000: 19.3, 21.6, 29.3).
+constexpr int kWideSortRows = 640;
+
+// Threads of k_row_hist (four soundings each).  Every block reserves its range
+// of each row that it meets by an atomic on the row's counter, so soundings in
+// no particular order cost rows x blocks atomics on as many addresses as rows:
+// fewer, larger blocks for large calls (500k uniform soundings in 377 rows: 256
+// threads 16.7 us, 512 12.3, 1024 10.0), smaller ones where they would leave
+// CUs idle (20k: 5.7, 5.8, 6.7) and for the batch (98, 98, 101).
+constexpr int kHistT = 512, kHistTWide = 1024;
+constexpr int64_t kHistWideFrom = 65536;  // soundings
+
 // Single-item kernels.  Dynamic LDS: 8-byte aligned base.
 __global__ __launch_bounds__(kThreads) void k_row_fill(RowItem it)
 {
@@ -841,10 +891,11 @@ __global__ __launch_bounds__(kThreads) void k_row_fill(RowItem it)
         it.stats[threadIdx.x] = 0;
 }
 
-__global__ __launch_bounds__(kThreads) void k_row_hist(RowItem it)
+template <int kT>
+__global__ __launch_bounds__(kT) void k_row_hist(RowItem it)
 {
     extern __shared__ unsigned long long s_dyn[];
-    row_hist_block(it, blockIdx.x, reinterpret_cast<int *>(s_dyn));
+    row_hist_block<kT>(it, blockIdx.x, reinterpret_cast<int *>(s_dyn));
 }
 
 __global__ __launch_bounds__(kThreads) void k_row_scatter(RowItem it)
@@ -854,12 +905,12 @@ __global__ __launch_bounds__(kThreads) void k_row_scatter(RowItem it)
     row_scatter_block(it, blockIdx.x, reinterpret_cast<int *>(s_dyn), lds);
 }
 
-template <int kKA, int kSU>
-__global__ __launch_bounds__(kThreads) void k_row_sort(RowItem it)
+template <int kT, int kKA, int kSU>
+__global__ __launch_bounds__(kT) void k_row_sort(RowItem it)
 {
     extern __shared__ unsigned long long s_dyn[];
-    __shared__ int lds[kThreads / 64];
-    row_sort_block<kKA, kSU>(it, blockIdx.x, reinterpret_cast<int *>(s_dyn + kKA), s_dyn, lds);
+    __shared__ int lds[kT / 64];
+    row_sort_block<kT, kKA, kSU>(it, blockIdx.x, reinterpret_cast<int *>(s_dyn + kKA), s_dyn, lds);
 }
 
 // Batched kernels: block b belongs to item item_of(off, count, b); the LDS is
@@ -874,12 +925,12 @@ __global__ __launch_bounds__(kThreads) void k_row_fill_batch(const RowItem *item
         it.stats[threadIdx.x] = 0;
 }
 
-__global__ __launch_bounds__(kThreads) void k_row_hist_batch(const RowItem *items,
+__global__ __launch_bounds__(kHistT) void k_row_hist_batch(const RowItem *items,
                                                              const int32_t *off, int count)
 {
     extern __shared__ unsigned long long s_dyn[];
     const int i = item_of(off, count, blockIdx.x);
-    row_hist_block(items[i], blockIdx.x - off[i], reinterpret_cast<int *>(s_dyn));
+    row_hist_block<kHistT>(items[i], blockIdx.x - off[i], reinterpret_cast<int *>(s_dyn));
 }
 
 __global__ __launch_bounds__(kThreads) void k_row_scatter_batch(const RowItem *items,
@@ -891,15 +942,15 @@ __global__ __launch_bounds__(kThreads) void k_row_scatter_batch(const RowItem *i
     row_scatter_block(items[i], blockIdx.x - off[i], reinterpret_cast<int *>(s_dyn), lds);
 }
 
-template <int kKA, int kSU>
-__global__ __launch_bounds__(kThreads) void k_row_sort_batch(const RowItem *items,
-                                                             const int32_t *off, int count)
+template <int kT, int kKA, int kSU>
+__global__ __launch_bounds__(kT) void k_row_sort_batch(const RowItem *items, const int32_t *off,
+                                                       int count, int block0)
 {
     extern __shared__ unsigned long long s_dyn[];
-    __shared__ int lds[kThreads / 64];
-    const int i = item_of(off, count, blockIdx.x);
-    row_sort_block<kKA, kSU>(items[i], blockIdx.x - off[i],
-                             reinterpret_cast<int *>(s_dyn + kKA), s_dyn, lds);
+    __shared__ int lds[kT / 64];
+    const int b = block0 + (int)blockIdx.x, i = item_of(off, count, b);
+    row_sort_block<kT, kKA, kSU>(items[i], b - off[i], reinterpret_cast<int *>(s_dyn + kKA), s_dyn,
+                                 lds);
 }
 
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -1012,13 +1063,12 @@ RowItem make_row_item(const auv_grid *g, const BinGeom &geom, const double *x,
     it.s = geom.s;
     it.nbx = geom.nbx;
     it.nby = geom.nby;
-    it.nblk = n > 0 ? (int32_t)grid_for(n, kRowChunk) : 0;
+    it.nblk = row_hist_blocks(n);
     it.bbox = nullptr;
     it.row_count = w.row_count;
     it.row_start = w.row_start;
-    it.rowid = w.rowid;
+    it.rowcol = w.rowid;
     it.pos = w.slot;
-    it.colkey = w.key;
     it.drops = w.partials;
     it.cell_start = w.cell_start;
     it.rec = w.rec;
@@ -1042,20 +1092,33 @@ auv_status launch_binning(const auv_grid *g, const BinGeom &geom, const double *
     auto *stats = reinterpret_cast<unsigned long long *>(w.stats);
 
     if (row_path_ok(geom)) {
-        const RowItem it = make_row_item(g, geom, x, y, z, n, w);
+        RowItem it = make_row_item(g, geom, x, y, z, n, w);
         k_row_fill<<<1, kThreads, 0, st>>>(it);
-        if (n > 0)
-            k_row_hist<<<it.nblk, kThreads, row_hist_lds(geom.nby), st>>>(it);
+        if (n >= kHistWideFrom) {
+            it.nblk = (int32_t)grid_for(n, kHistTWide * kRowPerThread);
+            k_row_hist<kHistTWide><<<it.nblk, kHistTWide, row_hist_lds(geom.nby), st>>>(it);
+        } else if (n > 0) {
+            k_row_hist<kHistT><<<it.nblk, kHistT, row_hist_lds(geom.nby), st>>>(it);
+        }
         k_row_scatter<<<row_scatter_blocks(n), kThreads, row_scatter_lds(geom.nby), st>>>(it);
         const int sc = sort_config((double)n / std::max(1, geom.nby));
         const size_t sl = row_sort_lds(sort_config_ka(sc), geom.nbx);
         const unsigned sb = (unsigned)geom.nby;
-        if (sc == 0)
-            k_row_sort<1024, 4><<<sb, kThreads, sl, st>>>(it);
-        else if (sc == 1)
-            k_row_sort<2048, 8><<<sb, kThreads, sl, st>>>(it);
-        else
-            k_row_sort<4096, 12><<<sb, kThreads, sl, st>>>(it);
+        if (geom.nby <= kWideSortRows) {
+            if (sc == 0)
+                k_row_sort<512, 1024, 2><<<sb, 512, sl, st>>>(it);
+            else if (sc == 1)
+                k_row_sort<512, 2048, 4><<<sb, 512, sl, st>>>(it);
+            else
+                k_row_sort<512, 4096, 6><<<sb, 512, sl, st>>>(it);
+        } else {
+            if (sc == 0)
+                k_row_sort<256, 1024, 4><<<sb, 256, sl, st>>>(it);
+            else if (sc == 1)
+                k_row_sort<256, 2048, 8><<<sb, 256, sl, st>>>(it);
+            else
+                k_row_sort<256, 4096, 12><<<sb, 256, sl, st>>>(it);
+        }
         AUV_HIP(hipGetLastError());
         return AUV_OK;
     }
@@ -1087,15 +1150,20 @@ auv_status launch_binning(const auv_grid *g, const BinGeom &geom, const double *
 }
 
 
-int32_t row_hist_blocks(int64_t n) { return n > 0 ? (int32_t)grid_for(n, kRowChunk) : 0; }
+int32_t row_hist_blocks(int64_t n)
+{
+    return n > 0 ? (int32_t)grid_for(n, kHistT * kRowPerThread) : 0;
+}
 // at least one block: block 0 publishes the row starts even for no soundings
 int32_t row_scatter_blocks(int64_t n) { return (int32_t)grid_for(n, kThreads * kScatterPer); }
+
+int row_sort_class(double keys_per_row) { return sort_config(keys_per_row); }
 
 auv_status launch_binning_batch(const RowItem *d_items, const int32_t *d_hist_off,
                                 const int32_t *d_scatter_off, const int32_t *d_sort_off,
                                 int32_t count, int32_t hist_blocks, int32_t scatter_blocks,
-                                int32_t sort_blocks, int32_t max_nbx, int32_t max_nby,
-                                double keys_per_row, hipStream_t st)
+                                const RowSortClass (&classes)[kRowSortClasses],
+                                int32_t max_nbx, int32_t max_nby, hipStream_t st)
 {
     if (count <= 0)
         return AUV_OK;
@@ -1103,18 +1171,35 @@ auv_status launch_binning_batch(const RowItem *d_items, const int32_t *d_hist_of
         return fail(AUV_ERR_INVALID, "bin domain too large for the row path");
     k_row_fill_batch<<<count, kThreads, 0, st>>>(d_items);
     if (hist_blocks > 0)
-        k_row_hist_batch<<<hist_blocks, kThreads, row_hist_lds(max_nby), st>>>(d_items,
+        k_row_hist_batch<<<hist_blocks, kHistT, row_hist_lds(max_nby), st>>>(d_items,
                                                                              d_hist_off, count);
     k_row_scatter_batch<<<scatter_blocks, kThreads, row_scatter_lds(max_nby), st>>>(
         d_items, d_scatter_off, count);
-    const int sc = sort_config(keys_per_row);
-    const size_t sl = row_sort_lds(sort_config_ka(sc), max_nbx);
-    if (sc == 0)
-        k_row_sort_batch<1024, 4><<<sort_blocks, kThreads, sl, st>>>(d_items, d_sort_off, count);
-    else if (sc == 1)
-        k_row_sort_batch<2048, 8><<<sort_blocks, kThreads, sl, st>>>(d_items, d_sort_off, count);
-    else
-        k_row_sort_batch<4096, 12><<<sort_blocks, kThreads, sl, st>>>(d_items, d_sort_off, count);
+    for (int sc = 0; sc < kRowSortClasses; ++sc) {
+        const RowSortClass &c = classes[sc];
+        const int n = c.block1 - c.block0;
+        if (n <= 0)
+            continue;
+        const size_t sl = row_sort_lds(sort_config_ka(sc), c.max_nbx);
+        auto launch = [&](auto *kernel, int threads) {
+            kernel<<<n, threads, sl, st>>>(d_items, d_sort_off, count, c.block0);
+        };
+        if (n <= kWideSortRows) {
+            if (sc == 0)
+                launch(k_row_sort_batch<512, 1024, 2>, 512);
+            else if (sc == 1)
+                launch(k_row_sort_batch<512, 2048, 4>, 512);
+            else
+                launch(k_row_sort_batch<512, 4096, 6>, 512);
+        } else {
+            if (sc == 0)
+                launch(k_row_sort_batch<256, 1024, 4>, 256);
+            else if (sc == 1)
+                launch(k_row_sort_batch<256, 2048, 8>, 256);
+            else
+                launch(k_row_sort_batch<256, 4096, 12>, 256);
+        }
+    }
     AUV_HIP(hipGetLastError());
     return AUV_OK;
 }

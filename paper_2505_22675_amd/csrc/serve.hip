@@ -557,11 +557,12 @@ auv_status enqueue_launch(auv_session *s, const std::vector<Pick> &picks, int ta
     }
     const dim3 sgrid((unsigned)((most * 16 + kStageChunk - 1) / kStageChunk), (unsigned)sa.count);
     k_serve_stage<<<sgrid, kStageThreads, 0, st>>>(sa);
+    // a swath request fills a few rows of the vehicle's grid densely: the
+    // largest key area
+    RowSortClass classes[kRowSortClasses];
+    classes[kRowSortClasses - 1] = RowSortClass{0, sort_off[B], max_nbx};
     AUV_TRY_S(launch_binning_batch(d_rows, d_offs, d_offs + (B + 1), d_offs + 2 * (B + 1), B,
-                                   hist_off[B], scat_off[B], sort_off[B], max_nbx, max_nby,
-                                   // a swath request fills a few rows of the vehicle's
-                                   // grid densely: the largest key area
-                                   1e30, st));
+                                   hist_off[B], scat_off[B], classes, max_nbx, max_nby, st));
     // as many persistent blocks as fit at once (8 waves per CU)
     const int per_cu = std::max(1, 8 / kServeParts);
     const int blocks = (int)std::min<int64_t>((int64_t)per_cu * s->cus, 16 + ntot / 256);
