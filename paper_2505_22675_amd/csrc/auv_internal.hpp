@@ -174,12 +174,13 @@ struct RowSortClass {
     int32_t max_nbx = 0;  // most bin columns of its items (sizes the LDS)
 };
 int row_sort_class(double keys_per_row);
-// max_nbx / max_nby: the largest bin domain among the items (sizes the LDS).
+// max_nbx / max_nby: the largest bin domain among the items (sizes the LDS);
+// boxes: every item has a bbox to widen.
 auv_status launch_binning_batch(const RowItem *d_items, const int32_t *d_hist_off,
                                 const int32_t *d_scatter_off, const int32_t *d_sort_off,
                                 int32_t count, int32_t hist_blocks, int32_t scatter_blocks,
                                 const RowSortClass (&classes)[kRowSortClasses],
-                                int32_t max_nbx, int32_t max_nby, hipStream_t st);
+                                int32_t max_nbx, int32_t max_nby, bool boxes, hipStream_t st);
 
 // The work of auv_bin_points into a caller-provided handle (no allocation).
 auv_status bin_into(const auv_grid *grid, const double *x, const double *y, const double *z,

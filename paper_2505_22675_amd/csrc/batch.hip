@@ -84,15 +84,17 @@ __global__ __launch_bounds__(256, 8) void k_idw_batch_sparse(const IdwItem *__re
     const int tx = 2 * ux + (wave & 1), ty = sub * uy + (wave >> 1);
     if ((wave >> 1) >= sub || tx * 8 >= it.a.nx || ty * 8 >= it.a.ny)
         return;
-    // integer powers share one variant (the power is a runtime value there);
-    // a general power needs the rescaling variant
-    if constexpr (kGeneral) {
-        if (it.pmode == 0) {
-            gather::gather_tile<3, 0, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
-            return;
-        }
+    // an instantiation per integer power (a test of the power at every visit
+    // costs a tenth) and one for a general power, with its rescaled sums
+    if (it.pmode == 2) {
+        gather::gather_tile<3, 2, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
+    } else if (it.pmode == 1) {
+        gather::gather_tile<3, 1, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
+    } else if (it.pmode == 3) {
+        gather::gather_tile<3, 3, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
+    } else if constexpr (kGeneral) {
+        gather::gather_tile<3, 0, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
     }
-    gather::gather_tile<3, -1, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
 }
 
 // Dense: one node tile of 64 nodes per block.
@@ -549,7 +551,7 @@ auv_status enqueue_batched(auv_batch *b, char *ws, hipStream_t st)
     const int nr = b->nrow_items;
     AUV_TRY_S(launch_binning_batch(t.rows, t.offs, t.offs + (nr + 1), t.offs + 2 * (nr + 1), nr,
                                    b->hist_blocks, b->scatter_blocks, b->sort_class, b->max_nbx,
-                                   b->max_nby, st));
+                                   b->max_nby, false, st));
     for (int i = 0; i < count; ++i) {
         if (row_path_ok(b->geom[i]))
             continue;

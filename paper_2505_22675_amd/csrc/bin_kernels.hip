@@ -322,7 +322,8 @@ constexpr int kMaxRowsLds = 8192;        // bin rows in the LDS histogram (15 bi
 constexpr int kScatterPer = 4;           // soundings per thread in k_row_scatter
 constexpr int kRunsMax = 8;              // row runs per wave for the grouped reservation
 
-template <int kT>
+// kBox: the binned soundings' lattice box is wanted (it.bbox).
+template <int kT, bool kBox>
 __device__ void row_hist_block(const RowItem &it, int blk, int *s_cnt)
 {
     typedef int v4i __attribute__((ext_vector_type(4)));
@@ -366,10 +367,12 @@ __device__ void row_hist_block(const RowItem &it, int blk, int *s_cnt)
                     rec[i] = v4i{X, Y, (int)rr, __float_as_int((float)zi)};
                     col[j] = (X + hB) >> s;
                     row[j] = (Y + hB) >> s;
-                    blx = min(blx, X);
-                    bhx = max(bhx, X);
-                    bly = min(bly, Y);
-                    bhy = max(bhy, Y);
+                    if constexpr (kBox) {
+                        blx = min(blx, X);
+                        bhx = max(bhx, X);
+                        bly = min(bly, Y);
+                        bhy = max(bhy, Y);
+                    }
                 } else {
                     out += 1;
                 }
@@ -420,7 +423,7 @@ __device__ void row_hist_block(const RowItem &it, int blk, int *s_cnt)
             pos[i] = row[j] >= 0 ? s_cnt[row[j]] + lr[j] : 0;
         }
     }
-    if (it.bbox) {
+    if constexpr (kBox) {
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) {
             blx = min(blx, __shfl_xor(blx, d, 64));
@@ -428,11 +431,29 @@ __device__ void row_hist_block(const RowItem &it, int blk, int *s_cnt)
             bhx = max(bhx, __shfl_xor(bhx, d, 64));
             bhy = max(bhy, __shfl_xor(bhy, d, 64));
         }
-        if (lane_id() == 0 && blx <= bhx) {
-            atomicMin(&it.bbox[0], blx);
-            atomicMin(&it.bbox[1], bly);
-            atomicMax(&it.bbox[2], bhx);
-            atomicMax(&it.bbox[3], bhy);
+        // one update per block: the waves' would queue at the same addresses
+        __shared__ int s_box[kT / 64][4];
+        if (lane_id() == 0) {
+            int *const o = s_box[threadIdx.x >> 6];
+            o[0] = blx;
+            o[1] = bly;
+            o[2] = bhx;
+            o[3] = bhy;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kT / 64; ++w) {
+                blx = min(blx, s_box[w][0]);
+                bly = min(bly, s_box[w][1]);
+                bhx = max(bhx, s_box[w][2]);
+                bhy = max(bhy, s_box[w][3]);
+            }
+            if (blx <= bhx) {
+                atomicMin(&it.bbox[0], blx);
+                atomicMin(&it.bbox[1], bly);
+                atomicMax(&it.bbox[2], bhx);
+                atomicMax(&it.bbox[3], bhy);
+            }
         }
     }
     // per-block drop counters (summed by block 0 of k_row_scatter: a device-wide atomic on
@@ -895,7 +916,7 @@ template <int kT>
 __global__ __launch_bounds__(kT) void k_row_hist(RowItem it)
 {
     extern __shared__ unsigned long long s_dyn[];
-    row_hist_block<kT>(it, blockIdx.x, reinterpret_cast<int *>(s_dyn));
+    row_hist_block<kT, false>(it, blockIdx.x, reinterpret_cast<int *>(s_dyn));
 }
 
 __global__ __launch_bounds__(kThreads) void k_row_scatter(RowItem it)
@@ -925,12 +946,13 @@ __global__ __launch_bounds__(kThreads) void k_row_fill_batch(const RowItem *item
         it.stats[threadIdx.x] = 0;
 }
 
+template <bool kBox>
 __global__ __launch_bounds__(kHistT) void k_row_hist_batch(const RowItem *items,
                                                              const int32_t *off, int count)
 {
     extern __shared__ unsigned long long s_dyn[];
     const int i = item_of(off, count, blockIdx.x);
-    row_hist_block<kHistT>(items[i], blockIdx.x - off[i], reinterpret_cast<int *>(s_dyn));
+    row_hist_block<kHistT, kBox>(items[i], blockIdx.x - off[i], reinterpret_cast<int *>(s_dyn));
 }
 
 __global__ __launch_bounds__(kThreads) void k_row_scatter_batch(const RowItem *items,
@@ -1163,7 +1185,7 @@ auv_status launch_binning_batch(const RowItem *d_items, const int32_t *d_hist_of
                                 const int32_t *d_scatter_off, const int32_t *d_sort_off,
                                 int32_t count, int32_t hist_blocks, int32_t scatter_blocks,
                                 const RowSortClass (&classes)[kRowSortClasses],
-                                int32_t max_nbx, int32_t max_nby, hipStream_t st)
+                                int32_t max_nbx, int32_t max_nby, bool boxes, hipStream_t st)
 {
     if (count <= 0)
         return AUV_OK;
@@ -1171,8 +1193,9 @@ auv_status launch_binning_batch(const RowItem *d_items, const int32_t *d_hist_of
         return fail(AUV_ERR_INVALID, "bin domain too large for the row path");
     k_row_fill_batch<<<count, kThreads, 0, st>>>(d_items);
     if (hist_blocks > 0)
-        k_row_hist_batch<<<hist_blocks, kHistT, row_hist_lds(max_nby), st>>>(d_items,
-                                                                             d_hist_off, count);
+        (boxes ? k_row_hist_batch<true> : k_row_hist_batch<false>)<<<hist_blocks, kHistT,
+                                                                     row_hist_lds(max_nby), st>>>(
+            d_items, d_hist_off, count);
     k_row_scatter_batch<<<scatter_blocks, kThreads, row_scatter_lds(max_nby), st>>>(
         d_items, d_scatter_off, count);
     for (int sc = 0; sc < kRowSortClasses; ++sc) {

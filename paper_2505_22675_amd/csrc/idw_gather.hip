@@ -14,8 +14,10 @@ void launch_pmode(const auv_bin_view &bv, const IdwArgs &a, const WinGeom &g, hi
     const dim3 grid((unsigned)nt), block(64);
     if (kMode == 2 || a.pmode == 2)
         k_idw_gather<kMode, 2, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
-    else if (a.pmode != 0)
-        k_idw_gather<kMode, -1, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
+    else if (a.pmode == 1)
+        k_idw_gather<kMode, 1, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
+    else if (a.pmode == 3)
+        k_idw_gather<kMode, 3, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
     else
         k_idw_gather<kMode, 0, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
 }

@@ -81,13 +81,15 @@ struct Acc {
     float emax = -kFar;  // running log2 weight maximum (general power)
 };
 
-// Adds a member at squared distance d2 with depth dz above the reference.
-template <int kPmode>
+// Adds a member at squared distance d2 with depth dz above the reference; a hit
+// (coincident sounding) counts with the weight kHitW where kHits (integer powers).
+template <int kPmode, bool kHits = false>
 __device__ __forceinline__ void add_weight(const IdwArgs &a, float d2, float dz, float &num,
-                                           float &den, float &emax)
+                                           float &den, float &emax, bool hit = false)
 {
     if constexpr (kPmode != 0) {
-        const float w = win::weight_nonhit(d2, kPmode > 0 ? kPmode : a.pmode);
+        const float w = kHits && hit ? win::kHitW
+                                     : win::weight_nonhit(d2, kPmode);
         num = fmaf(w, dz, num);
         den += w;
     } else {
@@ -171,11 +173,19 @@ struct Batches {
 
 // kGen: any node lattice and any radius (nodes with residuals, offsets of any
 // size); else the linear lattice of g with offsets below 2^24.
+//
+// Accumulate mode (kMode bit 2; integer powers, no cap): the wave takes every
+// nparts-th batch of the tile's soundings, starting at batch `part`, and returns
+// its nodes' sums in *acc_out and their reference depth in *zref_out; hits count
+// with the weight kHitW.
 template <int kMode, int kPmode, bool kGen>
 __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArgs &a,
-                                            const WinGeom &g, int tx, int ty, Smem &sm)
+                                            const WinGeom &g, int tx, int ty, Smem &sm,
+                                            int part = 0, int nparts = 1, Acc *acc_out = nullptr,
+                                            float *zref_out = nullptr)
 {
     constexpr bool kIdw = (kMode & 1) != 0;
+    constexpr bool kAccum = (kMode & 4) != 0;
     const int lane = threadIdx.x & 63;
     const int tb0 = tx * 8, ta0 = ty * 8;
     const int lb = lane & 7, la = lane >> 3;  // this lane's node in the tile
@@ -311,7 +321,9 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
     auto each = [&](auto &&f) {
         Batches it(bv, R, Xo, x_last, Yo, y_last);
         int k, have;
-        while ((have = it.next(&k)) > 0) {
+        for (int batch = 0; (have = it.next(&k)) > 0; ++batch) {
+            if (kAccum && batch % nparts != part)
+                continue;
             const int n = stage(k, have);
             f(n);
         }
@@ -341,13 +353,14 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
                         A.bidx = nearer ? id : A.bidx;
                         A.bz = nearer ? q[u].x : A.bz;
                     }
-                    A.bd2 = dense::dmin(A.bd2, D2);
+                    if constexpr (!kAccum)
+                        A.bd2 = dense::dmin(A.bd2, D2);
                     if constexpr (kIdw) {
                         const float fx = kGen ? dx + (p[u].z - rx) : dx + p[u].z;
                         const float fy = kGen ? dy + (p[u].w - ry) : dy + p[u].w;
                         const float d2 = fmaf(fx, fx, fy * fy);
-                        add_weight<kPmode>(a, kGen ? fmaxf(d2, 0x1p-40f) : d2, q[u].y, A.num, A.den,
-                                           A.emax);
+                        add_weight<kPmode, kAccum>(a, kGen ? fmaxf(d2, 0x1p-40f) : d2, q[u].y,
+                                                   A.num, A.den, A.emax, D2 == 0.0);
                         A.cnt += 1;
                         A.lo = min32(A.lo, q[u].x);
                         A.hi = max32(A.hi, q[u].x);
@@ -357,6 +370,11 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
         }
     });
 
+    if constexpr (kAccum) {
+        *acc_out = A;
+        *zref_out = zref;
+        return;
+    }
     const size_t tbase = (size_t)ta0 * a.nx + tb0;
     const uint32_t ob = (uint32_t)(la * a.nx + lb) << 2;
     const bool hit = A.bd2 == 0.0;

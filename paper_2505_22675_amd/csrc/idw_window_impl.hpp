@@ -530,19 +530,13 @@ struct WinSmem {
     float4 *rv;                 //   variant coordinates, depth   [64] (variants, unpacked)
 };
 
-// part / nparts: the wave takes every nparts-th 64-wide chunk of the tile's
-// candidates, starting at chunk `part` (several waves can share one tile).
-// In accumulate mode with nparts > 1 the wave leaves its partial sums in LDS
-// and its reference depth in *zref_out; the caller combines the parts.
 template <int kMode, int kPmode, bool kPacked, int kChunks, int kPrec>
 __device__ void window_tile(const auv_bin_view &bv, const IdwArgs &a, const WinGeom &g,
-                            int tile, int ntx, const WinSmem &sm, int part = 0,
-                            int nparts = 1, float *zref_out = nullptr)
+                            int tile, int ntx, const WinSmem &sm)
 {
     constexpr bool kIdw = (kMode & 1) != 0;
-    // the nearest key serves the nearest outputs, hits and the cap; the
-    // accumulate mode (no cap) recognises hits by their weight instead
-    constexpr bool kKey = kPacked && (kMode & 4) == 0;
+    // the nearest key serves the nearest outputs, hits and the cap
+    constexpr bool kKey = kPacked;
     // Accumulators are updated by plain LDS read-modify-write: within one
     // instruction every lane owns a distinct node, and a wave's LDS operations
     // complete in order, so no atomics are needed (LDS atomics would serialise
@@ -660,30 +654,28 @@ __device__ void window_tile(const auv_bin_view &bv, const IdwArgs &a, const WinG
         }
         const int total = __shfl(inc, 63, 64);
         if (r0 == 0) {
-            if constexpr ((kMode & 4) == 0) {
-                if (total == 0 && nrows <= kMaxRows) {
-                    // no sounding can reach the tile: its outputs are empty
-                    const size_t tbase = (size_t)ta0 * a.nx + tb0;
-                    for (int q0 = 0; q0 < kTW * TH; q0 += 64) {
-                        const int qq = q0 + lane;
-                        const int la = qq / kTW, lb = qq - la * kTW;
-                        if (la < th && lb < tw) {
-                            const uint32_t ob = (uint32_t)(la * a.nx + lb) << 2;
-                            if (kMode & 2) {
-                                if (a.nn_idx_out)
-                                    *byte_at(a.nn_idx_out + tbase, ob) = -1;
-                                if (a.nn_z_out)
-                                    *byte_at(a.nn_z_out + tbase, ob) = NAN;
-                            }
-                            if constexpr (kIdw) {
-                                if (a.cnt_out)
-                                    *byte_at(a.cnt_out + tbase, ob) = 0;
-                                *byte_at(a.z_out + tbase, ob) = NAN;
-                            }
+            if (total == 0 && nrows <= kMaxRows) {
+                // no sounding can reach the tile: its outputs are empty
+                const size_t tbase = (size_t)ta0 * a.nx + tb0;
+                for (int q0 = 0; q0 < kTW * TH; q0 += 64) {
+                    const int qq = q0 + lane;
+                    const int la = qq / kTW, lb = qq - la * kTW;
+                    if (la < th && lb < tw) {
+                        const uint32_t ob = (uint32_t)(la * a.nx + lb) << 2;
+                        if (kMode & 2) {
+                            if (a.nn_idx_out)
+                                *byte_at(a.nn_idx_out + tbase, ob) = -1;
+                            if (a.nn_z_out)
+                                *byte_at(a.nn_z_out + tbase, ob) = NAN;
+                        }
+                        if constexpr (kIdw) {
+                            if (a.cnt_out)
+                                *byte_at(a.cnt_out + tbase, ob) = 0;
+                            *byte_at(a.z_out + tbase, ob) = NAN;
                         }
                     }
-                    return;
                 }
+                return;
             }
             clear_acc();
         }
@@ -695,7 +687,7 @@ __device__ void window_tile(const auv_bin_view &bv, const IdwArgs &a, const WinG
         if (lane == 0)
             s_off[nr] = total;
         __syncthreads();
-        for (int c0 = part * 64; c0 < total; c0 += nparts * 64) {
+        for (int c0 = 0; c0 < total; c0 += 64) {
             const int gi = c0 + lane;
             bool keep = false;
             int px = 0, py = 0, pia = 0, pjb = 0, pidx = 0;
@@ -951,133 +943,101 @@ __device__ void window_tile(const auv_bin_view &bv, const IdwArgs &a, const WinG
         }
     }
     __syncthreads();
-    if constexpr ((kMode & 4) != 0) {
-        if (nparts > 1) {
-            *zref_out = zref;  // partial sums stay in LDS for the caller
-            return;
-        }
-    }
 
     // finalize: one node per lane, four passes over the tile
     const int kcap = a.max_pts;
     const unsigned long long imask = (1ull << kb) - 1ull;
-    if constexpr ((kMode & 4) != 0) {
-        for (int q0 = 0; q0 < kTW * TH; q0 += 64) {
-            const int qq = q0 + lane;
-            const int la = qq / kTW, lb = qq - la * kTW;
-            const int q = la * kRS + lb;
-            const bool act = la < th && lb < tw;
-            const int cnt = s_cnt[q];
-            // accumulate mode (no cap): add this tile's sums into the resident
-            // per-node accumulators, re-referenced from the tile's depth to
-            // the accumulators' depth.  One lane owns each node; the caller
-            // guarantees that no other wave updates the same node meanwhile.
-            if (act && cnt > 0) {
-                const int64_t o = (int64_t)(ta0 + la) * a.nx + tb0 + lb;
-                const float2 nd = s_nd[q];
-                const double shift = (double)zref - a.zref_acc;
-                const float lo = s_lo[q], hi = s_hi[q];
-                const int c0 = a.acc_cnt[o];
-                a.acc_num[o] += (float)((double)nd.x + (double)nd.y * shift);
-                a.acc_den[o] += nd.y;
-                a.acc_cnt[o] = c0 + cnt;
-                a.acc_lo[o] = c0 > 0 ? fminf(a.acc_lo[o], lo) : lo;
-                a.acc_hi[o] = c0 > 0 ? fmaxf(a.acc_hi[o], hi) : hi;
-            }
-        }
-    } else {
-        // outputs: the tile's first node as a scalar base, 32-bit byte
-        // offsets per lane (rows of the tile lie within 2^30 nodes of it).
-        // The nearest depth gathered in one pass is stored in the next, so
-        // the gather overlaps a pass of work (the passes are unrolled: in a
-        // loop, carrying the gathered value to the next iteration made the
-        // compiler wait for it at the end of its own pass).
-        constexpr int kPass = kTW * kTH / 64;
-        const size_t tbase = (size_t)ta0 * a.nx + tb0;
-        unsigned overm = 0u;  // bit p: this lane's node of pass p is over the cap
-        float bz_prev = NAN;
-        uint32_t ob_prev = 0;
-        bool st_prev = false;
+    // outputs: the tile's first node as a scalar base, 32-bit byte
+    // offsets per lane (rows of the tile lie within 2^30 nodes of it).
+    // The nearest depth gathered in one pass is stored in the next, so
+    // the gather overlaps a pass of work (the passes are unrolled: in a
+    // loop, carrying the gathered value to the next iteration made the
+    // compiler wait for it at the end of its own pass).
+    constexpr int kPass = kTW * kTH / 64;
+    const size_t tbase = (size_t)ta0 * a.nx + tb0;
+    unsigned overm = 0u;  // bit p: this lane's node of pass p is over the cap
+    float bz_prev = NAN;
+    uint32_t ob_prev = 0;
+    bool st_prev = false;
 #pragma unroll
-        for (int p = 0; p < kPass; ++p) {
-            const int qq = p * 64 + lane;
-            const int la = qq / kTW, lb = qq - la * kTW;
-            const int q = la * kRS + lb;
-            const bool act = p * 64 < kTW * TH && la < th && lb < tw;
-            const int cnt = s_cnt[q];
-            // the node's sums and bounds read with its count and key, one
-            // wait for all (the reads are in bounds for every lane)
-            const float2 ndv = s_nd[q];
-            const float lov = s_lo[q], hiv = s_hi[q];
-            int bi;
-            bool hit;
-            if constexpr (kKey) {
-                const unsigned long long key = s_key[q];
-                asm volatile("" ::"v"(cnt), "v"(key), "v"(ndv.x), "v"(ndv.y), "v"(lov), "v"(hiv));
-                bi = (int)(key & imask);
-                hit = (key >> kb) == 0ull;
-            } else if constexpr (kPacked) {
-                bi = 0;
-                hit = false;
-            } else {
-                bi = s_bidx[q];
-                hit = s_bd2[q] == 0.0;
-            }
-            const bool over = act && kcap > 0 && cnt > kcap;
-            overm |= over ? 1u << p : 0u;
-            const uint32_t ob = (uint32_t)(la * a.nx + lb) << 2;
-            float bz = NAN;
-            if (act && !over) {
-                if (kMode & 2) {
-                    if (a.nn_idx_out)
-                        *byte_at(a.nn_idx_out + tbase, ob) = cnt > 0 ? bi : -1;
-                    if (a.nn_z_out && cnt > 0) {
-                        if constexpr (kPacked)
-                            bz = __int_as_float(byte_at(bv.rec, (uint32_t)bi << 4)->w);
-                        else
-                            bz = s_bz[q];
-                    }
-                }
-                if constexpr (kIdw) {
-                    if (a.cnt_out)
-                        *byte_at(a.cnt_out + tbase, ob) = cnt;
-                    // a hit (best D^2 == 0) carries a dominant weight, so the
-                    // ratio is the mean of the hits, and it beats min_pts
-                    const bool hole = cnt == 0 || (cnt < a.min_pts && !hit);
-                    const float2 nd = ndv;
-                    // the quotient num / den and the return to absolute depth
-                    // in FP64 (the hardware reciprocal refined by a Newton
-                    // step, then one residual correction of the quotient),
-                    // rounded once to FP32 and clamped to the members' depths
-                    // (FP32 values, and rounding is monotonic, so this equals
-                    // clamping before the rounding)
-                    const float v = (float)((double)zref + quotient64(nd.x, nd.y));
-                    *byte_at(a.z_out + tbase, ob) = hole ? NAN : fminf(fmaxf(v, lov), hiv);
-                }
-            }
+    for (int p = 0; p < kPass; ++p) {
+        const int qq = p * 64 + lane;
+        const int la = qq / kTW, lb = qq - la * kTW;
+        const int q = la * kRS + lb;
+        const bool act = p * 64 < kTW * TH && la < th && lb < tw;
+        const int cnt = s_cnt[q];
+        // the node's sums and bounds read with its count and key, one
+        // wait for all (the reads are in bounds for every lane)
+        const float2 ndv = s_nd[q];
+        const float lov = s_lo[q], hiv = s_hi[q];
+        int bi;
+        bool hit;
+        if constexpr (kKey) {
+            const unsigned long long key = s_key[q];
+            asm volatile("" ::"v"(cnt), "v"(key), "v"(ndv.x), "v"(ndv.y), "v"(lov), "v"(hiv));
+            bi = (int)(key & imask);
+            hit = (key >> kb) == 0ull;
+        } else if constexpr (kPacked) {
+            bi = 0;
+            hit = false;
+        } else {
+            bi = s_bidx[q];
+            hit = s_bd2[q] == 0.0;
+        }
+        const bool over = act && kcap > 0 && cnt > kcap;
+        overm |= over ? 1u << p : 0u;
+        const uint32_t ob = (uint32_t)(la * a.nx + lb) << 2;
+        float bz = NAN;
+        if (act && !over) {
             if (kMode & 2) {
-                if (a.nn_z_out && st_prev)
-                    *byte_at(a.nn_z_out + tbase, ob_prev) = bz_prev;
+                if (a.nn_idx_out)
+                    *byte_at(a.nn_idx_out + tbase, ob) = cnt > 0 ? bi : -1;
+                if (a.nn_z_out && cnt > 0) {
+                    if constexpr (kPacked)
+                        bz = __int_as_float(byte_at(bv.rec, (uint32_t)bi << 4)->w);
+                    else
+                        bz = s_bz[q];
+                }
             }
-            bz_prev = bz;
-            ob_prev = ob;
-            st_prev = act && !over;
+            if constexpr (kIdw) {
+                if (a.cnt_out)
+                    *byte_at(a.cnt_out + tbase, ob) = cnt;
+                // a hit (best D^2 == 0) carries a dominant weight, so the
+                // ratio is the mean of the hits, and it beats min_pts
+                const bool hole = cnt == 0 || (cnt < a.min_pts && !hit);
+                const float2 nd = ndv;
+                // the quotient num / den and the return to absolute depth
+                // in FP64 (the hardware reciprocal refined by a Newton
+                // step, then one residual correction of the quotient),
+                // rounded once to FP32 and clamped to the members' depths
+                // (FP32 values, and rounding is monotonic, so this equals
+                // clamping before the rounding)
+                const float v = (float)((double)zref + quotient64(nd.x, nd.y));
+                *byte_at(a.z_out + tbase, ob) = hole ? NAN : fminf(fmaxf(v, lov), hiv);
+            }
         }
         if (kMode & 2) {
             if (a.nn_z_out && st_prev)
                 *byte_at(a.nn_z_out + tbase, ob_prev) = bz_prev;
         }
-        // nodes above the cap: re-done exactly by the whole wave
+        bz_prev = bz;
+        ob_prev = ob;
+        st_prev = act && !over;
+    }
+    if (kMode & 2) {
+        if (a.nn_z_out && st_prev)
+            *byte_at(a.nn_z_out + tbase, ob_prev) = bz_prev;
+    }
+    // nodes above the cap: re-done exactly by the whole wave
 #pragma unroll 1
-        for (int p = 0; p < kPass; ++p) {
-            unsigned long long om = __ballot((overm >> p) & 1u);
-            while (om) {
-                const int l = __ffsll((long long)om) - 1;
-                om &= om - 1;
-                const int qn = p * 64 + l;
-                exact_node<kMode, kPmode, kPrec>(bv, a, g.X0, g.Y0, g.DXl, g.DYl, ta0 + qn / kTW,
-                                                 tb0 + qn % kTW, zref);
-            }
+    for (int p = 0; p < kPass; ++p) {
+        unsigned long long om = __ballot((overm >> p) & 1u);
+        while (om) {
+            const int l = __ffsll((long long)om) - 1;
+            om &= om - 1;
+            const int qn = p * 64 + l;
+            exact_node<kMode, kPmode, kPrec>(bv, a, g.X0, g.Y0, g.DXl, g.DYl, ta0 + qn / kTW,
+                                             tb0 + qn % kTW, zref);
         }
     }
 }

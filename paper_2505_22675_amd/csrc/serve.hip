@@ -9,16 +9,16 @@
 //   batched row binning (the kernels behind auv_bin_points); its histogram
 //                       kernel also widens each request's lattice bounding
 //                       box over the binned soundings
-//   k_serve_update<c>   persistent: (request, node tile) work over the tiles
-//                       within the radius of each request's bounding box;
-//                       the window-form gather accumulates the tile in LDS
-//                       (16 waves per tile, combined in fixed order), then
-//                       each node's resident sums get one read-modify-write
+//   k_serve_update      (request, node tile) work over the tiles within the
+//                       radius of each request's bounding box: the gather
+//                       form accumulates the tile's 8 x 8 nodes (8 waves per
+//                       tile, combined in fixed order), then each node's
+//                       resident sums get one read-modify-write
 //   an event, which the worker thread observes to complete the tickets.
 // A vehicle has at most one request per launch and launches run in stream
 // order, so a vehicle's sums see its requests in submission order and no two
 // waves update one node at the same time.
-#include "idw_window_impl.hpp"
+#include "idw_gather_impl.hpp"
 
 #include <algorithm>
 #include <atomic>
@@ -45,7 +45,6 @@ struct ServeItem {
     auv_bin_view bv;
     IdwArgs a;
     WinGeom g;
-    int32_t ntx;
     const int32_t *bbox;  // X min, Y min, X max, Y max (lattice units, binned soundings)
 };
 
@@ -55,43 +54,39 @@ __device__ inline long long floor_div(long long a, long long b)
     return (a % b != 0 && (a < 0) != (b < 0)) ? q - 1 : q;
 }
 
-// Persistent update over (request, tile) work, one tile per block of
-// kServeParts waves.  A request's soundings are dense, so one wave per tile
-// would run hundreds of window visits in series: the waves of the block take
-// interleaved chunks of the tile's candidates into their own LDS sums, which
-// are then combined in wave order (so the result does not depend on timing)
-// and added to the resident sums with one read-modify-write per node.  Lane i
-// of every wave holds request i's tile rectangle (count <= 64); a wave-wide
-// prefix turns the pulled work index into (request, tile).  A request
-// covers few tiles (about 85 for 26k soundings), far fewer than the chip has
-// SIMDs, so a tile's latency is the request's: 16 waves per tile (96 KB of
-// LDS, one block per CU) measured p50 0.16 ms against 0.21 ms with 4.
-constexpr int kServeParts = 16;
-static_assert(win::kNodes <= 64 * kServeParts, "at most one node per thread when combining");
+// Update over (request, tile) work, one tile of 8 x 8 nodes per block of
+// kServeParts waves at a time.  A request's soundings are dense, so one wave per
+// tile would run its visits in series: the waves of the block take interleaved
+// batches of the tile's candidates into their own registers; the parts are then
+// combined in wave order (so the result does not depend on timing) and added to
+// the resident sums with one read-modify-write per node.  Lane i of every wave
+// holds request i's tile rectangle (count <= 64); a wave-wide prefix turns the
+// block's work index into (request, tile).
+//
+// A request covers few tiles (about 340 for 26k soundings, fewer than the chip
+// has SIMDs), so a tile's latency is the request's.  Against 16 x 16-node tiles
+// of the window form with 16 waves (sums in 96 KB of LDS), 26k soundings: 43 -> 20
+// us, three such requests 57 -> 28 (16 parts 25 and 45, 4 parts 31 and 37; the
+// power as a runtime value 24 and 32).
+constexpr int kServeParts = 8;
+constexpr int kServeTile = 8;
+constexpr int kServeBlocksPerCu = 4;
 
-template <int kChunks>
-__global__ __launch_bounds__(64 * kServeParts) void k_serve_update(
-    const ServeItem *__restrict__ items, int count, int32_t *__restrict__ counter)
+template <int kPmode, bool kGen>
+__global__ __launch_bounds__(64 * kServeParts, 8) void k_serve_update(
+    const ServeItem *__restrict__ items, int count)
 {
-    __shared__ float2 s_nd[kServeParts][win::kAcc];
-    __shared__ int s_cnt[kServeParts][win::kAcc];
-    __shared__ float s_lo[kServeParts][win::kAcc];
-    __shared__ float s_hi[kServeParts][win::kAcc];
-    __shared__ float s_emax[1];
-    __shared__ int s_beg[kServeParts][win::kMaxRows];
-    __shared__ int s_off[kServeParts][win::kMaxRows + 1];
-    __shared__ int4 s_rec[kServeParts][win::kRecSlots];
+    __shared__ gather::Smem s_gather[kServeParts];
+    __shared__ float4 s_sum[kServeParts][64];  // weighted depth, weight, smallest, largest depth
+    __shared__ int s_cnt[kServeParts][64];
     __shared__ float s_zref[kServeParts];
-    __shared__ int s_task;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const win::WinSmem sm{s_nd[wave], s_cnt[wave], s_lo[wave], s_hi[wave], nullptr, nullptr, nullptr,
-                          nullptr, s_emax, s_beg[wave], s_off[wave], s_rec[wave],
-                          s_rec[wave] + 1, nullptr};
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
     int t0x = 0, t0y = 0, tcols = 1, nt = 0;
     if (lane < count) {
         const ServeItem &it = items[lane];
         const int4 bb = *reinterpret_cast<const int4 *>(it.bbox);
-        if (it.g.nchunks == kChunks && bb.x <= bb.z && bb.y <= bb.w) {
+        if (bb.x <= bb.z && bb.y <= bb.w) {
             // nodes with a lattice coordinate within R of the box
             const long long R = it.a.R;
             const long long b0 = max(0ll, -floor_div(-((long long)bb.x - R - it.g.X0), it.g.DXl));
@@ -101,10 +96,10 @@ __global__ __launch_bounds__(64 * kServeParts) void k_serve_update(
             const long long a1 = min((long long)it.a.ny - 1,
                                      floor_div((long long)bb.w + R - it.g.Y0, it.g.DYl));
             if (b0 <= b1 && a0 <= a1) {
-                t0x = (int)(b0 / win::kTW);
-                t0y = (int)(a0 / win::kTH);
-                tcols = (int)(b1 / win::kTW) - t0x + 1;
-                nt = tcols * ((int)(a1 / win::kTH) - t0y + 1);
+                t0x = (int)(b0 / kServeTile);
+                t0y = (int)(a0 / kServeTile);
+                tcols = (int)(b1 / kServeTile) - t0x + 1;
+                nt = tcols * ((int)(a1 / kServeTile) - t0y + 1);
             }
         }
     }
@@ -117,48 +112,42 @@ __global__ __launch_bounds__(64 * kServeParts) void k_serve_update(
     }
     const int total = __shfl(incl, 63, 64);
     const int excl = incl - nt;
-    for (;;) {
-        if (threadIdx.x == 0)
-            s_task = atomicAdd(counter, 1);
-        __syncthreads();
-        const int t = s_task;
-        __syncthreads();  // every wave has its task before s_task is rewritten
-        if (t >= total)
-            break;
+    for (int t = blockIdx.x; t < total; t += gridDim.x) {
         const int i = __ffsll((long long)__ballot(incl > t)) - 1;
         const int loc = t - __builtin_amdgcn_readlane(excl, i);
         const int c = __builtin_amdgcn_readlane(tcols, i);
         const int tx = __builtin_amdgcn_readlane(t0x, i) + loc % c;
         const int ty = __builtin_amdgcn_readlane(t0y, i) + loc / c;
         const ServeItem &it = items[i];
+        gather::Acc A;
         float zr = 0.0f;
-        win::window_tile<5, -1, true, kChunks, AUV_P_FP32_REBASE>(
-            it.bv, it.a, it.g, ty * it.ntx + tx, it.ntx, sm, wave, kServeParts, &zr);
+        gather::gather_tile<5, kPmode, kGen>(it.bv, it.a, it.g, tx, ty, s_gather[wave], wave,
+                                             kServeParts, &A, &zr);
+        s_sum[wave][lane] = make_float4(A.num, A.den, A.lo, A.hi);
+        s_cnt[wave][lane] = A.cnt;
         if (lane == 0)
             s_zref[wave] = zr;
         __syncthreads();
-        // combine the parts in wave order: one node per thread
-        const int tb0 = tx * win::kTW, ta0 = ty * win::kTH;
-        const int la = threadIdx.x / win::kTW, lb = threadIdx.x - la * win::kTW;
-        const int q = la * win::kRS + lb;
-        if (la < min(win::kTH, it.a.ny - ta0) && lb < min(win::kTW, it.a.nx - tb0)) {
+        const int a = ty * kServeTile + (lane >> 3), b = tx * kServeTile + (lane & 7);
+        if (wave == 0 && a < it.a.ny && b < it.a.nx) {
+            // the parts in wave order, one node per lane
             double num = 0.0;
             float den = 0.0f, lo = INFINITY, hi = -INFINITY;
             int cnt = 0;
 #pragma unroll
             for (int w = 0; w < kServeParts; ++w) {
-                const int cw = s_cnt[w][q];
+                const int cw = s_cnt[w][lane];
                 if (cw > 0) {
-                    const float2 nd = s_nd[w][q];
-                    num += (double)nd.x + (double)nd.y * ((double)s_zref[w] - it.a.zref_acc);
-                    den += nd.y;
+                    const float4 p = s_sum[w][lane];
+                    num += (double)p.x + (double)p.y * ((double)s_zref[w] - it.a.zref_acc);
+                    den += p.y;
                     cnt += cw;
-                    lo = fminf(lo, s_lo[w][q]);
-                    hi = fmaxf(hi, s_hi[w][q]);
+                    lo = fminf(lo, p.z);
+                    hi = fmaxf(hi, p.w);
                 }
             }
             if (cnt > 0) {
-                const int64_t o = (int64_t)(ta0 + la) * it.a.nx + tb0 + lb;
+                const int64_t o = (int64_t)a * it.a.nx + b;
                 const int c0 = it.a.acc_cnt[o];
                 it.a.acc_num[o] += (float)num;
                 it.a.acc_den[o] += den;
@@ -315,7 +304,7 @@ struct Launch {
 
 // Launch table: device copy of what the kernels of one launch read.
 struct TableLayout {
-    size_t items, rows, offs, counters, bytes;
+    size_t items, rows, offs, bytes;
 };
 
 TableLayout table_layout()
@@ -328,8 +317,6 @@ TableLayout table_layout()
     o += align256(sizeof(RowItem) * kMaxBatchReq);
     t.offs = o;
     o += align256(sizeof(int32_t) * 3 * (kMaxBatchReq + 1));
-    t.counters = o;
-    o += align256(sizeof(int32_t) * 4);
     t.bytes = o;
     return t;
 }
@@ -484,10 +471,8 @@ auv_status enqueue_launch(auv_session *s, const std::vector<Pick> &picks, int ta
     int32_t *offs = reinterpret_cast<int32_t *>(th + L.offs);
     const int B = (int)picks.size();
     int32_t *hist_off = offs, *scat_off = offs + (B + 1), *sort_off = offs + 2 * (B + 1);
-    int32_t *counters = reinterpret_cast<int32_t *>(th + L.counters);
     hist_off[0] = scat_off[0] = sort_off[0] = 0;
-    bool chunks[win::kMaxChunks + 1] = {false, false, false, false, false};
-    int64_t ntot = 0;
+    bool linear = true;  // every grid's offsets fit the linear gather form
     int32_t max_nbx = 0, max_nby = 0;
     for (int i = 0; i < B; ++i) {
         const Pick &p = picks[i];
@@ -524,23 +509,18 @@ auv_status enqueue_launch(auv_session *s, const std::vector<Pick> &picks, int ta
         it.a.acc_lo = acc + 3 * plane;
         it.a.acc_hi = acc + 4 * plane;
         it.g = V.wg;
-        it.ntx = (V.grid.d.nx + win::kTW - 1) / win::kTW;
         it.bbox = reinterpret_cast<const int32_t *>(dev);
-        chunks[V.wg.nchunks] = true;
+        linear = linear && gather::gather_linear(V.wg, V.geom.R);
         hist_off[i + 1] = hist_off[i] + row_hist_blocks(p.n);
         scat_off[i + 1] = scat_off[i] + row_scatter_blocks(p.n);
         sort_off[i + 1] = sort_off[i] + V.geom.nby;
         max_nbx = std::max(max_nbx, V.geom.nbx);
         max_nby = std::max(max_nby, V.geom.nby);
-        ntot += p.n;
     }
-    for (int c = 0; c < 4; ++c)
-        counters[c] = 0;
     // device pointers inside the table
     ServeItem *d_items = reinterpret_cast<ServeItem *>(td + L.items);
     RowItem *d_rows = reinterpret_cast<RowItem *>(td + L.rows);
     int32_t *d_offs = reinterpret_cast<int32_t *>(td + L.offs);
-    int32_t *d_counters = reinterpret_cast<int32_t *>(td + L.counters);
     hipStream_t st = s->stream;
     // the table and the requests reach the device through one staging kernel
     StageArgs sa;
@@ -562,19 +542,18 @@ auv_status enqueue_launch(auv_session *s, const std::vector<Pick> &picks, int ta
     RowSortClass classes[kRowSortClasses];
     classes[kRowSortClasses - 1] = RowSortClass{0, sort_off[B], max_nbx};
     AUV_TRY_S(launch_binning_batch(d_rows, d_offs, d_offs + (B + 1), d_offs + 2 * (B + 1), B,
-                                   hist_off[B], scat_off[B], classes, max_nbx, max_nby, st));
-    // as many persistent blocks as fit at once (8 waves per CU)
-    const int per_cu = std::max(1, 8 / kServeParts);
-    const int blocks = (int)std::min<int64_t>((int64_t)per_cu * s->cus, 16 + ntot / 256);
-    const int threads = 64 * kServeParts;
-    if (chunks[1])
-        k_serve_update<1><<<blocks, threads, 0, st>>>(d_items, B, d_counters + 0);
-    if (chunks[2])
-        k_serve_update<2><<<blocks, threads, 0, st>>>(d_items, B, d_counters + 1);
-    if (chunks[3])
-        k_serve_update<3><<<blocks, threads, 0, st>>>(d_items, B, d_counters + 2);
-    if (chunks[4])
-        k_serve_update<4><<<blocks, threads, 0, st>>>(d_items, B, d_counters + 3);
+                                   hist_off[B], scat_off[B], classes, max_nbx, max_nby, true,
+                                   st));
+    // the tiles are known on the device only: as many blocks as fit at once
+    const int blocks = kServeBlocksPerCu * s->cus, threads = 64 * kServeParts;
+    auto update = [&](auto *kernel) { kernel<<<blocks, threads, 0, st>>>(d_items, B); };
+    const int pmode = s->veh[picks[0].vehicle].base.pmode;  // the session's power
+    if (pmode == 1)
+        update(linear ? k_serve_update<1, false> : k_serve_update<1, true>);
+    else if (pmode == 2)
+        update(linear ? k_serve_update<2, false> : k_serve_update<2, true>);
+    else
+        update(linear ? k_serve_update<3, false> : k_serve_update<3, true>);
     AUV_HIP(hipGetLastError());
     AUV_HIP(hipEventRecord(ev, st));
     return AUV_OK;
