@@ -17,15 +17,14 @@
 // depths.  Sums are relative to the depth of the tile's first record.  A node
 // with coincident soundings (D^2 == 0) takes their mean depth.
 //
-// What bounds it: instruction issue on large grids (a SIMD issues about one
-// instruction in 2.2 clocks, scalar ones included; about 450 vector and 250
-// scalar ones per 64 nodes), the latency of one wave's chain of reads on small
+// What bounds it: vector instruction issue on large grids (490 vector and 330
+// scalar instructions per 64 nodes of the 2M-sounding swath; a SIMD issues a
+// vector one in 4.2 clocks), the latency of one wave's chain of reads on small
 // ones.  Against the window form it replaces (16 x 16 nodes per wave, LDS
 // accumulators, over-cap nodes one at a time), on an MI355X, whole calls with
-// their binning: 20k soundings on 256^2 nodes, 121-node disks 76 -> 39 us;
-// 150k swath soundings on 1023 x 769, cap 16, 71 -> 48 us; nearest only, 500k
-// on 2048 x 1500, 108 -> 84 us; 2M swath soundings on 4096^2 366 -> 358 us;
-// against the tile kernel, 120k on 701 x 650 at 3.3 m 89 -> 47 us.
+// their binning when it came: 20k soundings on 256^2 nodes, 121-node disks 76 -> 39 us; 150k swath
+// soundings on 1023 x 769, cap 16, 71 -> 48 us; nearest only, 500k on 2048 x 1500,
+// 108 -> 84 us; against the tile kernel, 120k on 701 x 650 at 3.3 m 89 -> 47 us.
 #pragma once
 #include "idw_dense_impl.hpp"
 #include "idw_window_impl.hpp"
@@ -279,13 +278,15 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
             return e * e;
         };
         const float ex0 = valid ? gap2(xr, xq[0], xq[1]) : INFINITY;
-        const float ex1 = valid ? gap2(xr, xq[2], xq[3]) : INFINITY;
-        const float ey0 = reach2 - gap2(yr, yq[0], yq[1]), ey1 = reach2 - gap2(yr, yq[2], yq[3]);
+        const float ex1 = valid && cx ? gap2(xr, xq[2], xq[3]) : INFINITY;
+        const float ey0 = reach2 - gap2(yr, yq[0], yq[1]);
+        const float ey1 = (cy ? reach2 : -1.0f) - gap2(yr, yq[2], yq[3]);
+        // this lane's record reaches the quarter (none reaches those past the grid)
+        const bool in[4] = {ex0 <= ey0, ex1 <= ey0, ex0 <= ey1, ex1 <= ey1};
         unsigned long long m[4];
-        m[0] = __ballot(ex0 <= ey0);
-        m[1] = cx ? __ballot(ex1 <= ey0) : 0ull;
-        m[2] = cy ? __ballot(ex0 <= ey1) : 0ull;
-        m[3] = cx && cy ? __ballot(ex1 <= ey1) : 0ull;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            m[q] = __ballot(in[q]);
         const unsigned long long any = m[0] | m[1] | m[2] | m[3];
         if (any == 0ull)
             return 0;
@@ -308,7 +309,7 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
         for (int q = 0; q < 4; ++q) {
             const int slot = __builtin_amdgcn_mbcnt_hi((unsigned)(m[q] >> 32),
                                                        __builtin_amdgcn_mbcnt_lo((unsigned)m[q], 0u));
-            if ((m[q] >> lane) & 1ull)
+            if (in[q])
                 sm.list[q][slot] = (uint16_t)(lane * sizeof(Rec));
             n = max(n, (int)__popcll(m[q]));
         }
@@ -395,7 +396,9 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
         }
     }
     if constexpr (kIdw) {
-        if (__any(hit)) {
+        // (both branches are marked rare: otherwise the registers of the rounds
+        // below push the common path's values to scratch, 219 -> 203 us)
+        if (__builtin_expect(__any(hit), 0)) {
             // coincident soundings: the node takes their mean depth
             double hsum = 0.0;
             int hcnt = 0;
@@ -411,7 +414,7 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
             if (hit && act && !over)
                 *win::byte_at(a.z_out + tbase, ob) = (float)(hsum / (double)hcnt);
         }
-        if (__any(over)) {
+        if (__builtin_expect(__any(over), 0)) {
             // The cap nearest of every node above the cap, in rounds of kRound:
             // each round keeps in a sorted register list the smallest keys above
             // the previous round's, and sums them in key order.
