@@ -240,6 +240,11 @@ auv_status launch_idw_window(const auv_bin_view &bins, const IdwArgs &a, const W
 bool gather_covers(const auv_bin_view &bv, const IdwArgs &a);
 auv_status launch_idw_gather(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g,
                              hipStream_t st);
+// The dense form by the gather form's lists: whether it covers a call (bins of at
+// least the radius), and its launch.
+bool gather_top_covers(const auv_bin_view &bv, const IdwArgs &a);
+auv_status launch_idw_gather_top(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g,
+                                 hipStream_t st);
 auv_status launch_idw_dense(const auv_bin_view &bins, const IdwArgs &a, int pmode,
                             hipStream_t st);
 auv_status launch_idw_window_prec(const auv_bin_view &bins, const IdwArgs &a,

@@ -31,7 +31,45 @@ void launch_lattice(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g, 
         launch_pmode<kMode, true>(bv, a, WinGeom{}, st);
 }
 
+template <int kMode>
+void launch_top(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g, hipStream_t st)
+{
+    const int ntx = (a.nx + 7) / 8, nt = ntx * ((a.ny + 7) / 8);
+    auto launch = [&](auto *linear, auto *general) {
+        if (g && gather_linear(*g, a.R))
+            linear<<<(unsigned)nt, 64, 0, st>>>(bv, a, *g, ntx, nt);
+        else
+            general<<<(unsigned)nt, 64, 0, st>>>(bv, a, WinGeom{}, ntx, nt);
+    };
+    if (a.max_pts <= 8)
+        launch(k_idw_gather_top<kMode, 8, false>, k_idw_gather_top<kMode, 8, true>);
+    else if (a.max_pts <= 16)
+        launch(k_idw_gather_top<kMode, 16, false>, k_idw_gather_top<kMode, 16, true>);
+    else
+        launch(k_idw_gather_top<kMode, 32, false>, k_idw_gather_top<kMode, 32, true>);
+}
+
 }  // namespace
+
+bool gather_top_covers(const auv_bin_view &bv, const IdwArgs &a)
+{
+    return a.precision == AUV_P_FP32_REBASE && a.mode >= 1 && a.mode <= 3 && a.max_pts >= 1 &&
+           a.max_pts <= 32 && gather_ok(a.R, bv.idx_bits, a.max_pts) &&
+           (int64_t(1) << bv.bin_log2) >= a.R &&
+           (int64_t)((a.nx + 7) / 8) * ((a.ny + 7) / 8) < (int64_t(1) << 31);
+}
+
+auv_status launch_idw_gather_top(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g,
+                                 hipStream_t st)
+{
+    switch (a.mode) {
+    case 1: launch_top<1>(bv, a, g, st); break;
+    case 2: launch_top<2>(bv, a, g, st); break;
+    default: launch_top<3>(bv, a, g, st); break;
+    }
+    AUV_HIP(hipGetLastError());
+    return AUV_OK;
+}
 
 bool gather_covers(const auv_bin_view &bv, const IdwArgs &a)
 {

@@ -177,7 +177,11 @@ struct Batches {
 // nparts-th batch of the tile's soundings, starting at batch `part`, and returns
 // its nodes' sums in *acc_out and their reference depth in *zref_out; hits count
 // with the weight kHitW.
-template <int kMode, int kPmode, bool kGen>
+//
+// kTop > 0 (the dense form on bins of at least the radius): no sums, one pass that
+// keeps every node's kTop nearest in a sorted register list, then the dense form's
+// finish (max_pts <= kTop).
+template <int kMode, int kPmode, bool kGen, int kTop = 0>
 __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArgs &a,
                                             const WinGeom &g, int tx, int ty, Smem &sm,
                                             int part = 0, int nparts = 1, Acc *acc_out = nullptr,
@@ -330,6 +334,37 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
         }
     };
 
+    // keys of the capped selection: D^2 << kb | index, as dense_node's list entries
+    const int kb = max(bv.idx_bits, 12);
+    // the entry of the record at `off` where it is a member above `last`, else +inf
+    auto entry = [&](uint32_t off, double last) {
+        const Rec *r = rec_at(off);
+        const double D2 = d2_of(off_x(r->p), off_y(r->p));
+        // bits of D2 + 2^52: the integer D2 under an exponent that the shift by at
+        // least 12 drops; 2^52 added to the key makes it a normal number
+        const unsigned long long key =
+            (((unsigned long long)__double_as_longlong(D2 + 0x1p52)) << kb) | (unsigned)r->idx;
+        const double v = __longlong_as_double((long long)(key + (1ull << 52)));
+        return (D2 <= R2) & (v > last) ? v : __builtin_huge_val();
+    };
+    if constexpr (kTop > 0) {
+        double list[kTop];
+#pragma unroll
+        for (int u = 0; u < kTop; ++u)
+            list[u] = __builtin_huge_val();
+        each([&](int n) {
+#pragma unroll 1
+            for (int e = 0; e < n; e += 4) {
+                const uint2 o = *reinterpret_cast<const uint2 *>(lst + e);
+                dense::merge4(list, entry(o.x & 0xffffu, 0.0), entry(o.x >> 16, 0.0),
+                              entry(o.y & 0xffffu, 0.0), entry(o.y >> 16, 0.0));
+            }
+        });
+        if (act)
+            dense::dense_finish<kMode, kTop>(bv, a, tb0 + lb, ta0 + la, list, kb, a.pmode);
+        return;
+    }
+
     Acc A;
     each([&](int n) {
         // two records at a time (their reads overlap)
@@ -419,7 +454,6 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
             // each round keeps in a sorted register list the smallest keys above
             // the previous round's, and sums them in key order.
             constexpr int kRound = 8;
-            const int kb = max(bv.idx_bits, 12);
             const unsigned imask = (1u << bv.idx_bits) - 1u;
             double last = 0.0;  // key of the last member taken
             int bi = -1;
@@ -435,21 +469,8 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
                 each([&](int n) {
 #pragma unroll 1
                     for (int e0 = 0; e0 < n; e0 += 4) {
-                        double e[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const Rec *r = rec_at(lst[e0 + u]);
-                            const double D2 = d2_of(off_x(r->p), off_y(r->p));
-                            // bits of D2 + 2^52: the integer D2 under an exponent
-                            // that the shift by at least 12 drops; 2^52 added to
-                            // the key makes it a normal number
-                            const unsigned long long key =
-                                (((unsigned long long)__double_as_longlong(D2 + 0x1p52)) << kb) |
-                                (unsigned)r->idx;
-                            const double v = __longlong_as_double((long long)(key + (1ull << 52)));
-                            e[u] = (D2 <= R2) & (v > last) ? v : __builtin_huge_val();
-                        }
-                        dense::merge4(list, e[0], e[1], e[2], e[3]);
+                        dense::merge4(list, entry(lst[e0], last), entry(lst[e0 + 1], last),
+                                      entry(lst[e0 + 2], last), entry(lst[e0 + 3], last));
                     }
                 });
                 last = list[kRound - 1];
@@ -530,6 +551,27 @@ __global__ __launch_bounds__(64, 8) void k_idw_gather(auv_bin_view bv, IdwArgs a
     const int tile = win::xcd_tile(blockIdx.x, ntiles);
     const int ty = tile / ntx;
     gather_tile<kMode, kPmode, kGen>(bv, a, g, tile - ty * ntx, ty, sm);
+}
+
+// Waves per SIMD that the list leaves room for.
+constexpr int top_waves(int top) { return top == 8 ? 8 : top == 16 ? 5 : 3; }
+
+// The dense form on bins of at least the radius.  Its ring search reads nine
+// such bins per node whatever the density, five times the disk; the quarters'
+// lists hold about half of that, and every record is read once per tile instead
+// of once per node.  Bound by vector instruction issue (the list merges) and, at
+// one wave generation, by the chain of a tile's batches.  512^2 nodes, disks of
+// (cap): 20 (16) 50 -> 46 us, 9 (16) 31 -> 26, 30 (16) 68 -> 59, 5 (8) 23 -> 14, 20 (8)
+// 47 -> 31, 25 (24) 91 -> 83; finer bins keep the ring search (it stops after a few).
+template <int kMode, int kTop, bool kGen>
+__global__ __launch_bounds__(64, top_waves(kTop)) void k_idw_gather_top(auv_bin_view bv, IdwArgs a,
+                                                                      WinGeom g, int ntx,
+                                                                      int ntiles)
+{
+    __shared__ Smem sm;
+    const int tile = win::xcd_tile(blockIdx.x, ntiles);
+    const int ty = tile / ntx;
+    gather_tile<kMode, 0, kGen, kTop>(bv, a, g, tile - ty * ntx, ty, sm);
 }
 
 }  // namespace gather

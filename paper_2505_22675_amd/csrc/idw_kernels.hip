@@ -371,10 +371,14 @@ auv_status launch_idw(const auv_bin_view &bv, const IdwArgs &a_in, hipStream_t s
     else if (a.power == 3.0f)
         pmode = 3;
     a.pmode = pmode;
-    if (a.dense)
-        return launch_idw_dense(bv, a, pmode, st);
     WinGeom wg;
     const bool linear = window_geometry(a, &wg);
+    // The dense form: by the gather form's lists on bins of at least the radius,
+    // by its ring search on finer ones, where it stops after a few small bins.
+    if (a.dense && gather_top_covers(bv, a))
+        return launch_idw_gather_top(bv, a, linear ? &wg : nullptr, st);
+    if (a.dense)
+        return launch_idw_dense(bv, a, pmode, st);
     // The gather form takes every exact call that it covers: at 20k to 2M
     // soundings it was measured faster than the window form on linear lattices
     // (1.02 to 1.9 times) and than the tile kernel on the others (1.9 times).
