@@ -36,17 +36,17 @@ namespace {
 
 constexpr int kXcds = 8;
 constexpr int kRun = 64;  // consecutive units of one XCD
-constexpr int kForms = 3; // sparse, dense, span
+constexpr int kForms = 4; // sparse, dense, span, top
 constexpr int kBatchDenseK = 16;  // largest max_pts the batched dense kernel keeps
 
-enum { kSparse = 0, kDense = 1, kSpan = 2 };
+enum { kSparse = 0, kDense = 1, kSpan = 2, kTop = 3 };
 
 struct IdwItem {
     auv_bin_view bv;
     IdwArgs a;
     WinGeom g;
     int32_t ntx, ntiles;
-    int32_t form, pmode;  // form: kSparse, kDense or kSpan
+    int32_t form, pmode;  // form: kSparse, kDense (ring search), kSpan or kTop (dense by lists)
 };
 
 // The unit of block b out of n: blocks are dealt round-robin to the 8 XCDs,
@@ -106,6 +106,17 @@ __global__ __launch_bounds__(64) void k_idw_batch_dense(const IdwItem *__restric
     dense::dense_tile<3, kBatchDenseK>(it.bv, it.a, w.y, it.ntx, it.pmode);
 }
 
+// Dense by the gather form's lists: one tile of 8 x 8 nodes per block.
+__global__ __launch_bounds__(64, gather::top_waves(kBatchDenseK)) void k_idw_batch_top(
+    const IdwItem *__restrict__ items, const int2 *__restrict__ work, int n)
+{
+    __shared__ gather::Smem sm;
+    const int2 w = work[deal_unit(blockIdx.x, n)];
+    const IdwItem &it = items[w.x];
+    const int ty = w.y / it.ntx;
+    gather::gather_tile<3, 0, false, kBatchDenseK>(it.bv, it.a, it.g, w.y - ty * it.ntx, ty, sm);
+}
+
 // Span: one 16 x 16 node tile per block.
 __global__ __launch_bounds__(64) void k_idw_batch_span(const IdwItem *__restrict__ items,
                                                        const int2 *__restrict__ work, int n)
@@ -122,6 +133,8 @@ void launch_form(int form, bool general, const IdwItem *items, const int2 *work,
     const dim3 grid((unsigned)n);
     if (form == kDense)
         k_idw_batch_dense<<<grid, 64, 0, st>>>(items, work, n);
+    else if (form == kTop)
+        k_idw_batch_top<<<grid, 64, 0, st>>>(items, work, n);
     else if (form == kSpan)
         k_idw_batch_span<<<grid, 64, 0, st>>>(items, work, n);
     else if (general)
@@ -187,11 +200,17 @@ bool dense_allowed(const auv_batch_item &it)
 // soundings each, and the sort's bins and rows are short.  256 uneven tiles of
 // 1k-200k soundings, IDW and binning together: default side 4.95 ms, 0.7 / 1.0
 // / 1.4 / 2.0 times the distance 2.33 / 2.25 / 2.26 / 2.51 ms.
+//
+// Up to kTopPop caps per disk the default side stays: the form by lists takes
+// those items (limits of 1.0, 1.5 and 3 caps: the 256-tile batch 1738, 1738 and
+// 1743 us; the ring search on small bins for all of them 1768).
+constexpr double kTopPop = 1.5;
+
 int32_t dense_cell_log2(const auv_batch_item &it, int32_t R, int32_t s)
 {
     const double pop = disk_population(it);
     const double k = std::max(8, it.params.max_pts);
-    if (!(pop > k))
+    if (!(pop > kTopPop * k))
         return s;
     const int32_t c = (int32_t)std::lround(std::log2(1.2 * R * std::sqrt(k / pop)));
     return std::max<int32_t>(12, std::min(s, c));
@@ -275,7 +294,7 @@ struct auv_batch {
     std::vector<int2> work;
     int32_t hist_blocks = 0, scatter_blocks = 0, nrow_items = 0;
     auv::RowSortClass sort_class[auv::kRowSortClasses];
-    int32_t work_off[auv::kForms + 1] = {0, 0, 0, 0};  // each form's units in `work`
+    int32_t work_off[auv::kForms + 1] = {0};  // each form's units in `work`
     bool any_general = false;  // a sparse item with a general power
     int32_t max_nbx = 0, max_nby = 0;  // largest bin domain of the row-binned items
     hipStream_t cap_stream2 = nullptr;
@@ -412,6 +431,10 @@ bool make_idw_item(const auv_batch_item &it, const auv_bin_view &bv, const IdwAr
         d.form = kDense;
         ok = it.params.max_pts >= 1 && it.params.max_pts <= kBatchDenseK &&
              dense::dense_key_ok(a.R, bv.idx_bits);
+        // on bins of at least the radius by the gather form's lists (8 x 8 nodes)
+        if (ok && dense::dense_tile_w(a) == dense::kDT && gather_top_covers(bv, a) &&
+            window_geometry(a, &d.g) && gather::gather_linear(d.g, a.R))
+            d.form = kTop;
         const int tw = dense::dense_tile_w(a), th = 64 / tw;
         d.ntx = (it.grid.nx + tw - 1) / tw;
         d.ntiles = d.ntx * ((it.grid.ny + th - 1) / th);
@@ -446,7 +469,7 @@ auv_status build_tables(auv_batch *b, char *ws)
         IdwItem &d = b->idw[i];
         const bool ok = make_idw_item(it, bv, a, b->algo[i], &d) && row_path_ok(b->geom[i]);
         b->covered[i] = ok ? 1 : 0;
-        if (d.form == kDense) {
+        if (d.form == kDense || d.form == kTop) {
             tile_cost[i] = ((double)it.n + (double)it.grid.nx * it.grid.ny * 4.0) /
                            std::max(1, d.ntiles);
         } else {
@@ -570,16 +593,18 @@ auv_status enqueue_batched(auv_batch *b, char *ws, hipStream_t st)
         }
         return AUV_OK;
     };
-    // the dense form runs on a forked branch of the graph, concurrently
-    if (units(kDense) > 0) {
+    // the dense forms run on a forked branch of the graph, concurrently
+    const bool fork = units(kDense) > 0 || units(kTop) > 0;
+    if (fork) {
         AUV_HIP(hipEventRecord(b->ev_fork, st));
         AUV_HIP(hipStreamWaitEvent(b->cap_stream2, b->ev_fork, 0));
         AUV_TRY_S(launch(kDense, b->cap_stream2));
+        AUV_TRY_S(launch(kTop, b->cap_stream2));
         AUV_HIP(hipEventRecord(b->ev_join, b->cap_stream2));
     }
     AUV_TRY_S(launch(kSparse, st));
     AUV_TRY_S(launch(kSpan, st));
-    if (units(kDense) > 0)
+    if (fork)
         AUV_HIP(hipStreamWaitEvent(st, b->ev_join, 0));
     for (int i = 0; i < count; ++i) {
         if (b->covered[i])
