@@ -39,9 +39,9 @@ def host_threads() -> int:
 
 # Sources that define each profiled kernel (its code and its argument structs).
 KERNEL_SOURCES = {
-    "k_idw_window": ["idw_window_impl.hpp", "idw_window.hip", "auv_internal.hpp"],
+    "k_idw_gather": ["idw_gather_impl.hpp", "idw_gather.hip", "auv_internal.hpp"],
     "k_bilinear": ["bilinear_kernels.hip", "resample_axis.hpp", "auv_internal.hpp"],
-    "k_kriging": ["kriging.hip", "resample_axis.hpp", "auv_internal.hpp"],
+    "k_kriging_phase": ["kriging.hip", "resample_axis.hpp", "auv_internal.hpp"],
     "k_bicubic": ["bilinear_kernels.hip", "resample_axis.hpp", "auv_internal.hpp"],
 }
 
@@ -712,7 +712,7 @@ def main():
     dur = {"idw": st_ms[1], "bilinear": st_ms[2]}
     dom = max(dur, key=dur.get)
     achieved = alg[dom] / (dur[dom] * 1e-3) / 1e9
-    kernel_names = {"idw": "k_idw_window", "bilinear": "k_bilinear"}
+    kernel_names = {"idw": "k_idw_gather", "bilinear": "k_bilinear"}
     roofline = {"bound": "hbm", "kernel": kernel_names[dom], "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": None, "algorithmic_bytes": int(alg[dom]),
@@ -816,7 +816,7 @@ def main():
                "nodes_per_s": round(up.numel() / (krig_ms * 1e-3), 1),
                "achieved_GBs": round(krig_gbs, 1), "hbm_frac": round(krig_gbs / HBM_PEAK_GBS, 4),
                "nan_nodes": int(torch.isnan(krig).sum().item())}
-    kv = valu_from_profile("k_kriging")
+    kv = valu_from_profile("k_kriging_phase")
     kriging["valu_issue"] = None if kv is None else {
         "instructions": kv, "achieved_per_s": round(kv / (krig_ms * 1e-3), 1),
         "peak_per_s": VALU_ISSUE_PEAK, "frac": round(kv / (krig_ms * 1e-3) / VALU_ISSUE_PEAK, 4),
