@@ -412,7 +412,7 @@ def batched_report(ag, dev, reps=20, with_plain=True, tune_in=None, tune_out=Non
     """256 uneven tiles (1e3..2e5 soundings, 64^2..1024^2 nodes, p in {1,2,3}):
     the plain form (tile after tile, default bin size and kernel choice, no
     graph) against the batched form (autotuned per tile class, batched
-    binning, persistent kernels, one HIP graph)."""
+    binning, one IDW launch per kernel form, one HIP graph)."""
     import tempfile
 
     import numpy as np

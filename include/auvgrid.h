@@ -289,10 +289,10 @@ auv_status auv_grid_idw_noalloc(const auv_grid *grid, const double *x, const dou
 
 /* ------------------------------------------------------------ batches --
  * Many independent, uneven gridding problems ("items") run as one unit: one
- * set of batched binning launches and one persistent IDW launch per kernel
- * form (sparse window, dense top-k; on two concurrent graph branches) whose
- * waves pull (item, tile) work from per-XCD queues, captured once into a HIP
- * graph and replayed on later launches.  Bin sizes and the kernel form per item come
+ * set of batched binning launches and one IDW launch per kernel
+ * form (sparse, dense top-k; on two concurrent graph branches) over the
+ * (item, tile) units of all its items, captured once into a HIP graph and
+ * replayed on later launches.  Bin sizes and the kernel form per item come
  * from an autotune table (auv_batch_autotune) or from defaults.  Each item's
  * result is the auv_interp_idw result for that item (same definition and
  * tolerance); the batch only changes how the work is scheduled. */

@@ -22,9 +22,10 @@
 // vector one in 4.2 clocks), the latency of one wave's chain of reads on small
 // ones.  Against the window form it replaces (16 x 16 nodes per wave, LDS
 // accumulators, over-cap nodes one at a time), on an MI355X, whole calls with
-// their binning when it came: 20k soundings on 256^2 nodes, 121-node disks 76 -> 39 us; 150k swath
-// soundings on 1023 x 769, cap 16, 71 -> 48 us; nearest only, 500k on 2048 x 1500,
-// 108 -> 84 us; against the tile kernel, 120k on 701 x 650 at 3.3 m 89 -> 47 us.
+// their binning when it came: 20k soundings on 256^2 nodes, 121-node disks 76 ->
+// 39 us; 150k swath soundings on 1023 x 769, cap 16, 71 -> 48 us; nearest only,
+// 500k on 2048 x 1500, 108 -> 84 us; against the tile kernel, 120k on 701 x 650 at
+// 3.3 m 89 -> 47 us.
 #pragma once
 #include "idw_dense_impl.hpp"
 #include "idw_window_impl.hpp"

@@ -12,8 +12,7 @@
 //
 // Needs a linear node lattice (dx * 2^15 and dy * 2^15 integers, so
 // X_b = X_0 + b*DX exactly) and a window of at most 256 cells.  It serves the
-// resident sums of the serving path, the precision variants, the batch's sparse
-// items, and the calls beyond the gather form's caps and keys.
+// precision variants and the calls beyond the gather form's caps and keys.
 //
 // Exactness as in the tile kernel: membership, ranking and hits on the exact
 // lattice D^2 (64-bit integers), FP32 distances/weights from lattice offsets
