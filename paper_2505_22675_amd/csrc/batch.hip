@@ -250,6 +250,20 @@ std::vector<Choice> tile_variants(const Choice &c)
     return v;
 }
 
+// Most work units an item can have, whatever its form and node tile (the dense
+// form's tiles are any power-of-two shape of 64 nodes, the others larger than
+// 8 x 8).
+size_t most_units(const auv_batch_item &it)
+{
+    size_t most = 0;
+    for (int w = 1; w <= 64; w *= 2) {
+        const int h = 64 / w;
+        most = std::max(most, (size_t)((it.grid.nx + w - 1) / w) *
+                                  (size_t)((it.grid.ny + h - 1) / h));
+    }
+    return most;
+}
+
 // Candidate (bin size, form) pairs the autotuner may time for an item.
 std::vector<Choice> candidates(const auv_batch_item &it, int32_t sR)
 {
@@ -695,8 +709,7 @@ auv_status auv_batch_plan(const auv_batch_item *items, int32_t count, const char
                 need = std::max(need, bin_workspace_layout(it.n, gg, nullptr, nullptr));
         }
         b->slice_size[i] = align256(need);
-        const size_t tiles8 = (size_t)((it.grid.nx + 7) / 8) * ((it.grid.ny + 7) / 8);
-        max_tiles += tiles8;
+        max_tiles += most_units(it);
     }
     b->tables_bytes = align256(tables_size(count, max_tiles));
     off = b->tables_bytes;
@@ -847,7 +860,7 @@ auv_status auv_batch_autotune(const auv_batch_item *items, int32_t count, void *
     // the tables region of the workspace holds the throughput runs' work list
     size_t work_cap = 0;
     for (int k = 0; k < count; ++k)
-        work_cap += (size_t)((b->items[k].grid.nx + 7) / 8) * ((b->items[k].grid.ny + 7) / 8);
+        work_cap += most_units(b->items[k]);
     std::ostringstream table;
     table << "# auvgrid autotune table: class <log2 disk population> <log2 grid side> "
              "bin_log2 <s> algo <1 sparse | 2 dense> tile <nodes across> <nodes down> "

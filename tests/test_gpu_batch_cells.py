@@ -57,3 +57,38 @@ def test_dense_subdivided_bins(orc, n, nx, ny, r, cap, corner):
     ok = ~np.isnan(oz)
     assert (np.abs(gz[ok] - oz[ok]) / np.abs(oz[ok])).max() <= REL
     b.close()
+
+
+@pytest.mark.parametrize("tile", [(16, 4), (4, 16), (64, 1)])
+def test_dense_tiles_of_narrow_items(orc, tmp_path, tile):
+    """Items one node wide or high whose planned tile has more units than 8 x 8
+    tiles would: the work list has room for them."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_22675_amd as ag
+    rng = np.random.default_rng(5)
+    items, data = [], []
+    for k in range(60):
+        nx, ny = (1, 9) if k % 2 else (9, 1)
+        x, y = rng.uniform(-6, nx * 2.0 + 6, 300), rng.uniform(-6, ny * 2.0 + 6, 300)
+        z = -300.0 + rng.normal(0, 2.0, 300)
+        dev = [torch.from_numpy(a).cuda() for a in (x, y, z)]
+        zo = torch.full((ny, nx), -1.0, dtype=torch.float32, device="cuda")
+        prm = ag.idw_params(power=2.0, radius=6.0, min_pts=1, max_pts=16)
+        items.append(ag.batch_item(ag.make_desc(0.0, 0.0, 2.0, 2.0, nx, ny), *dev, prm, zo, None,
+                                   None))
+        data.append((nx, ny, x, y, z, zo, dev))
+    pop = 300 / ((1 * 2.0 + 12.0) * (9 * 2.0 + 12.0)) * np.pi * 36.0
+    table = tmp_path / "tune.txt"
+    table.write_text(f"class {int(np.floor(np.log2(pop + 1)))} {round(np.log2(9))} bin_log2 17 "
+                     f"algo {ag.AUV_ALGO_DENSE} tile {tile[0]} {tile[1]} ms 1\n")
+    b = ag.Batch(items, str(table))
+    assert all(b.item_plan_full(i) == (17, ag.AUV_ALGO_DENSE, *tile) for i in range(60))
+    b.launch()
+    torch.cuda.synchronize()
+    for nx, ny, x, y, z, zo, _ in data:
+        oz, _, _ = orc.idw(orc.Grid(0.0, 0.0, 2.0, 2.0, nx, ny), x, y, z, 6.0, 2.0, 1, 16,
+                           bin_log2=-1)
+        gz = zo.cpu().numpy().astype(np.float64)
+        assert (np.abs(gz - oz) / np.abs(oz)).max() <= REL
+    b.close()
