@@ -37,6 +37,7 @@ namespace {
 constexpr int kXcds = 8;
 constexpr int kRun = 64;  // consecutive units of one XCD
 constexpr int kForms = 4; // sparse, dense, span, top
+constexpr int kFewSortRows = 2560;  // ten bin rows per CU
 constexpr int kBatchDenseK = 16;  // largest max_pts the batched dense kernel keeps
 
 enum { kSparse = 0, kDense = 1, kSpan = 2, kTop = 3 };
@@ -498,7 +499,20 @@ auv_status build_tables(auv_batch *b, char *ws)
             tile_cost[i] = 20.0 + rho * bw * bh;
         }
     }
-    // row-binned items by the class of their rows' sort
+    // row-binned items by the class of their rows' sort; a batch of few rows takes
+    // one launch of the largest class instead (a launch costs more than the
+    // smaller key areas save there: 7 tiles 93 -> 86 us, 16 tiles 107 -> 103)
+    int64_t all_rows = 0;
+    int top_class = 0;
+    for (int i = 0; i < count; ++i) {
+        const BinGeom &g = b->geom[i];
+        if (!row_path_ok(g))
+            continue;
+        all_rows += g.nby;
+        top_class = std::max(top_class,
+                             row_sort_class((double)b->items[i].n / std::max(1, g.nby)));
+    }
+    const bool one_class = all_rows <= kFewSortRows;
     b->nrow_items = 0;
     for (int sc = 0; sc < kRowSortClasses; ++sc) {
         RowSortClass &c = b->sort_class[sc];
@@ -507,7 +521,10 @@ auv_status build_tables(auv_batch *b, char *ws)
         for (int i = 0; i < count; ++i) {
             const auv_batch_item &it = b->items[i];
             const BinGeom &g = b->geom[i];
-            if (!row_path_ok(g) || row_sort_class((double)it.n / std::max(1, g.nby)) != sc)
+            if (!row_path_ok(g))
+                continue;
+            if (sc != (one_class ? top_class
+                                 : row_sort_class((double)it.n / std::max(1, g.nby))))
                 continue;
             BinWorkspace w;
             bin_workspace_layout(it.n, g, ws + b->slice_off[i], &w);
