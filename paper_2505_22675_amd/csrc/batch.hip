@@ -203,9 +203,11 @@ bool dense_allowed(const auv_batch_item &it)
 // / 1.4 / 2.0 times the distance 2.33 / 2.25 / 2.26 / 2.51 ms.
 //
 // Up to kTopPop caps per disk the default side stays: the form by lists takes
-// those items (limits of 1.0, 1.5 and 3 caps: the 256-tile batch 1738, 1738 and
-// 1743 us; the ring search on small bins for all of them 1768).
-constexpr double kTopPop = 1.5;
+// those items.  Limits of 1.0, 1.5 and 3 caps: the 256-tile batch 1738, 1738 and
+// 1743 us (the ring search on small bins for all of them 1768); 4 tiles of which
+// one holds 1.9 caps per disk 81 us at 1.5 and 66 at 3 (a small batch is the
+// search's chain of bins), 6 such tiles 84 and 71.
+constexpr double kTopPop = 3.0;
 
 int32_t dense_cell_log2(const auv_batch_item &it, int32_t R, int32_t s)
 {
