@@ -243,14 +243,22 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
     auto rec_at = [&](uint32_t off) {
         return reinterpret_cast<const Rec *>(reinterpret_cast<const char *>(sm.rec) + off);
     };
-    // offset of a record from this lane's node (exact: both are integers)
+    // Offset of a record from this lane's node: an integer where kGen (offsets at
+    // the largest radius, 2^24, exceed the integers that FP32 holds), else FP32
+    // (exact: gather_linear keeps the offsets within reach below 2^24).
     auto off_x = [&](const float4 &p) {
-        return kGen ? (float)(__float_as_int(p.x) - xi) : p.x - xn;
+        if constexpr (kGen)
+            return __float_as_int(p.x) - xi;
+        else
+            return p.x - xn;
     };
     auto off_y = [&](const float4 &p) {
-        return kGen ? (float)(__float_as_int(p.y) - yi) : p.y - yn;
+        if constexpr (kGen)
+            return __float_as_int(p.y) - yi;
+        else
+            return p.y - yn;
     };
-    auto d2_of = [](float dx, float dy) {  // exact: |dx|, |dy| <= 2^24 within the radius
+    auto d2_of = [](auto dx, auto dy) {  // exact where |dx|, |dy| <= 2^26
         return fma((double)dx, (double)dx, (double)dy * (double)dy);
     };
     constexpr uint32_t kNullOff = kNull * sizeof(Rec);
@@ -381,7 +389,7 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const float dx = off_x(p[u]), dy = off_y(p[u]);
+                const auto dx = off_x(p[u]), dy = off_y(p[u]);
                 const double D2 = d2_of(dx, dy);
                 if (D2 <= R2) {
                     if constexpr ((kMode & 2) != 0) {
@@ -393,8 +401,8 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
                     if constexpr (!kAccum)
                         A.bd2 = dense::dmin(A.bd2, D2);
                     if constexpr (kIdw) {
-                        const float fx = kGen ? dx + (p[u].z - rx) : dx + p[u].z;
-                        const float fy = kGen ? dy + (p[u].w - ry) : dy + p[u].w;
+                        const float fx = (float)dx + (kGen ? p[u].z - rx : p[u].z);
+                        const float fy = (float)dy + (kGen ? p[u].w - ry : p[u].w);
                         const float d2 = fmaf(fx, fx, fy * fy);
                         add_weight<kPmode, kAccum>(a, kGen ? fmaxf(d2, 0x1p-40f) : d2, q[u].y,
                                                    A.num, A.den, A.emax, D2 == 0.0);
@@ -442,7 +450,7 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
 #pragma unroll 1
                 for (int e = 0; e < n; ++e) {
                     const Rec *r = rec_at(lst[e]);
-                    const bool h = off_x(r->p) == 0.0f && off_y(r->p) == 0.0f;
+                    const bool h = off_x(r->p) == 0 && off_y(r->p) == 0;
                     hsum += h ? (double)r->z : 0.0;
                     hcnt += h ? 1 : 0;
                 }
