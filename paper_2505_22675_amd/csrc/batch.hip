@@ -74,10 +74,11 @@ __device__ inline int deal_unit(int b, int n)
 // (8 per disk, no cap).
 template <bool kGeneral>
 __global__ __launch_bounds__(256, 8) void k_idw_batch_sparse(const IdwItem *__restrict__ items,
-                                                             const int2 *__restrict__ work, int n)
+                                                             const int2 *__restrict__ work, int n,
+                                                             int b0)
 {
     __shared__ gather::Smem sm[4];
-    const int2 w = work[deal_unit(blockIdx.x, n)];
+    const int2 w = work[deal_unit(b0 + (int)blockIdx.x, n)];
     const IdwItem &it = items[w.x];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int uy = w.y / it.ntx, ux = w.y - uy * it.ntx;
@@ -100,19 +101,20 @@ __global__ __launch_bounds__(256, 8) void k_idw_batch_sparse(const IdwItem *__re
 
 // Dense: one node tile of 64 nodes per block.
 __global__ __launch_bounds__(64) void k_idw_batch_dense(const IdwItem *__restrict__ items,
-                                                        const int2 *__restrict__ work, int n)
+                                                        const int2 *__restrict__ work, int n,
+                                                        int b0)
 {
-    const int2 w = work[deal_unit(blockIdx.x, n)];
+    const int2 w = work[deal_unit(b0 + (int)blockIdx.x, n)];
     const IdwItem &it = items[w.x];
     dense::dense_tile<3, kBatchDenseK>(it.bv, it.a, w.y, it.ntx, it.pmode);
 }
 
 // Dense by the gather form's lists: one tile of 8 x 8 nodes per block.
 __global__ __launch_bounds__(64, gather::top_waves(kBatchDenseK)) void k_idw_batch_top(
-    const IdwItem *__restrict__ items, const int2 *__restrict__ work, int n)
+    const IdwItem *__restrict__ items, const int2 *__restrict__ work, int n, int b0)
 {
     __shared__ gather::Smem sm;
-    const int2 w = work[deal_unit(blockIdx.x, n)];
+    const int2 w = work[deal_unit(b0 + (int)blockIdx.x, n)];
     const IdwItem &it = items[w.x];
     const int ty = w.y / it.ntx;
     gather::gather_tile<3, 0, false, kBatchDenseK>(it.bv, it.a, it.g, w.y - ty * it.ntx, ty, sm);
@@ -120,10 +122,11 @@ __global__ __launch_bounds__(64, gather::top_waves(kBatchDenseK)) void k_idw_bat
 
 // Span: one 16 x 16 node tile per block.
 __global__ __launch_bounds__(64) void k_idw_batch_span(const IdwItem *__restrict__ items,
-                                                       const int2 *__restrict__ work, int n)
+                                                       const int2 *__restrict__ work, int n,
+                                                       int b0)
 {
     __shared__ span::Smem<win::kTW, win::kTH> sm;
-    const int2 w = work[deal_unit(blockIdx.x, n)];
+    const int2 w = work[deal_unit(b0 + (int)blockIdx.x, n)];
     const IdwItem &it = items[w.x];
     span::span_tile<3, -1, win::kTW, win::kTH>(it.bv, it.a, it.g, w.y, it.ntx, sm);
 }
@@ -131,17 +134,25 @@ __global__ __launch_bounds__(64) void k_idw_batch_span(const IdwItem *__restrict
 void launch_form(int form, bool general, const IdwItem *items, const int2 *work, int n,
                  hipStream_t st)
 {
-    const dim3 grid((unsigned)n);
+    // HIP takes fewer than 2^32 threads per launch: the list goes in pieces (of
+    // whole runs on every XCD)
+    auto pieces = [&](auto *kernel, int threads) {
+        constexpr int kPiece = 1 << 23;
+        static_assert(kPiece % (kXcds * kRun) == 0, "pieces cut the dealt runs");
+        for (int64_t b0 = 0; b0 < n; b0 += kPiece)
+            kernel<<<(unsigned)std::min<int64_t>(kPiece, n - b0), threads, 0, st>>>(items, work, n,
+                                                                                    (int)b0);
+    };
     if (form == kDense)
-        k_idw_batch_dense<<<grid, 64, 0, st>>>(items, work, n);
+        pieces(k_idw_batch_dense, 64);
     else if (form == kTop)
-        k_idw_batch_top<<<grid, 64, 0, st>>>(items, work, n);
+        pieces(k_idw_batch_top, 64);
     else if (form == kSpan)
-        k_idw_batch_span<<<grid, 64, 0, st>>>(items, work, n);
+        pieces(k_idw_batch_span, 64);
     else if (general)
-        k_idw_batch_sparse<true><<<grid, 256, 0, st>>>(items, work, n);
+        pieces(k_idw_batch_sparse<true>, 256);
     else
-        k_idw_batch_sparse<false><<<grid, 256, 0, st>>>(items, work, n);
+        pieces(k_idw_batch_sparse<false>, 256);
 }
 
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }

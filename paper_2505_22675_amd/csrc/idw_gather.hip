@@ -1,25 +1,38 @@
 // Gather IDW form: launcher.  The per-tile code is in idw_gather_impl.hpp.
 #include "idw_gather_impl.hpp"
 
+#include <algorithm>
+
 namespace auv {
 
 using namespace gather;
 
 namespace {
 
+// One wave per tile.  HIP takes fewer than 2^32 threads per launch, so a grid of
+// 2^26 tiles or more (2^32 nodes) goes in pieces.
+template <class K>
+void launch_tiles(K *kernel, const auv_bin_view &bv, const IdwArgs &a, const WinGeom &g,
+                  hipStream_t st)
+{
+    constexpr int64_t kPiece = int64_t(1) << 25;
+    const int ntx = (a.nx + 7) / 8;
+    const int64_t nt = (int64_t)ntx * ((a.ny + 7) / 8);
+    for (int64_t t0 = 0; t0 < nt; t0 += kPiece)
+        kernel<<<(unsigned)std::min(kPiece, nt - t0), 64, 0, st>>>(bv, a, g, ntx, (int)nt, (int)t0);
+}
+
 template <int kMode, bool kGen>
 void launch_pmode(const auv_bin_view &bv, const IdwArgs &a, const WinGeom &g, hipStream_t st)
 {
-    const int ntx = (a.nx + 7) / 8, nt = ntx * ((a.ny + 7) / 8);
-    const dim3 grid((unsigned)nt), block(64);
     if (kMode == 2 || a.pmode == 2)
-        k_idw_gather<kMode, 2, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
+        launch_tiles(k_idw_gather<kMode, 2, kGen>, bv, a, g, st);
     else if (a.pmode == 1)
-        k_idw_gather<kMode, 1, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
+        launch_tiles(k_idw_gather<kMode, 1, kGen>, bv, a, g, st);
     else if (a.pmode == 3)
-        k_idw_gather<kMode, 3, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
+        launch_tiles(k_idw_gather<kMode, 3, kGen>, bv, a, g, st);
     else
-        k_idw_gather<kMode, 0, kGen><<<grid, block, 0, st>>>(bv, a, g, ntx, nt);
+        launch_tiles(k_idw_gather<kMode, 0, kGen>, bv, a, g, st);
 }
 
 template <int kMode>
@@ -34,12 +47,11 @@ void launch_lattice(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g, 
 template <int kMode>
 void launch_top(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g, hipStream_t st)
 {
-    const int ntx = (a.nx + 7) / 8, nt = ntx * ((a.ny + 7) / 8);
     auto launch = [&](auto *linear, auto *general) {
         if (g && gather_linear(*g, a.R))
-            linear<<<(unsigned)nt, 64, 0, st>>>(bv, a, *g, ntx, nt);
+            launch_tiles(linear, bv, a, *g, st);
         else
-            general<<<(unsigned)nt, 64, 0, st>>>(bv, a, WinGeom{}, ntx, nt);
+            launch_tiles(general, bv, a, WinGeom{}, st);
     };
     if (a.max_pts <= 8)
         launch(k_idw_gather_top<kMode, 8, false>, k_idw_gather_top<kMode, 8, true>);

@@ -552,12 +552,13 @@ __host__ __device__ inline bool gather_linear(const WinGeom &g, int32_t R)
     return (int64_t)R + 7ll * (g.DXl > g.DYl ? g.DXl : g.DYl) < (1ll << 24);
 }
 
+// tile0: first tile of the launch (a grid may take several, see launch_tiles)
 template <int kMode, int kPmode, bool kGen>
 __global__ __launch_bounds__(64, 8) void k_idw_gather(auv_bin_view bv, IdwArgs a, WinGeom g, int ntx,
-                                                   int ntiles)
+                                                   int ntiles, int tile0)
 {
     __shared__ Smem sm;
-    const int tile = win::xcd_tile(blockIdx.x, ntiles);
+    const int tile = win::xcd_tile(tile0 + (int)blockIdx.x, ntiles);
     const int ty = tile / ntx;
     gather_tile<kMode, kPmode, kGen>(bv, a, g, tile - ty * ntx, ty, sm);
 }
@@ -575,10 +576,10 @@ constexpr int top_waves(int top) { return top == 8 ? 8 : top == 16 ? 5 : 3; }
 template <int kMode, int kTop, bool kGen>
 __global__ __launch_bounds__(64, top_waves(kTop)) void k_idw_gather_top(auv_bin_view bv, IdwArgs a,
                                                                       WinGeom g, int ntx,
-                                                                      int ntiles)
+                                                                      int ntiles, int tile0)
 {
     __shared__ Smem sm;
-    const int tile = win::xcd_tile(blockIdx.x, ntiles);
+    const int tile = win::xcd_tile(tile0 + (int)blockIdx.x, ntiles);
     const int ty = tile / ntx;
     gather_tile<kMode, 0, kGen, kTop>(bv, a, g, tile - ty * ntx, ty, sm);
 }
