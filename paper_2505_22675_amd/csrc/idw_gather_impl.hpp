@@ -420,23 +420,23 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
         *zref_out = zref;
         return;
     }
-    const size_t tbase = (size_t)ta0 * a.nx + tb0;
-    const uint32_t ob = (uint32_t)(la * a.nx + lb) << 2;
+    // (64 bits: seven rows of 2^30 nodes are beyond any 32-bit offset)
+    const int64_t o = (int64_t)(ta0 + la) * a.nx + (tb0 + lb);
     const bool hit = A.bd2 == 0.0;
     const bool over = kIdw && act && a.max_pts > 0 && A.cnt > a.max_pts;
     if (act && !over) {
         if constexpr ((kMode & 2) != 0) {
             if (a.nn_idx_out)
-                *win::byte_at(a.nn_idx_out + tbase, ob) = A.bd2 < 1e300 ? A.bidx : -1;
+                gmem(a.nn_idx_out)[o] = A.bd2 < 1e300 ? A.bidx : -1;
             if (a.nn_z_out)
-                *win::byte_at(a.nn_z_out + tbase, ob) = A.bz;
+                gmem(a.nn_z_out)[o] = A.bz;
         }
         if constexpr (kIdw) {
             if (a.cnt_out)
-                *win::byte_at(a.cnt_out + tbase, ob) = A.cnt;
+                gmem(a.cnt_out)[o] = A.cnt;
             const bool hole = A.cnt == 0 || A.cnt < a.min_pts;
             const float v = (float)((double)zref + win::quotient64(A.num, A.den));
-            *win::byte_at(a.z_out + tbase, ob) = hole ? NAN : fminf(fmaxf(v, A.lo), A.hi);
+            gmem(a.z_out)[o] = hole ? NAN : fminf(fmaxf(v, A.lo), A.hi);
         }
     }
     if constexpr (kIdw) {
@@ -456,7 +456,7 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
                 }
             });
             if (hit && act && !over)
-                *win::byte_at(a.z_out + tbase, ob) = (float)(hsum / (double)hcnt);
+                gmem(a.z_out)[o] = (float)(hsum / (double)hcnt);
         }
         if (__builtin_expect(__any(over), 0)) {
             // The cap nearest of every node above the cap, in rounds of kRound:
@@ -518,14 +518,14 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
             if (over) {
                 if constexpr ((kMode & 2) != 0) {
                     if (a.nn_idx_out)
-                        *win::byte_at(a.nn_idx_out + tbase, ob) = bi;
+                        gmem(a.nn_idx_out)[o] = bi;
                     if (a.nn_z_out)
-                        *win::byte_at(a.nn_z_out + tbase, ob) = z0;
+                        gmem(a.nn_z_out)[o] = z0;
                 }
                 if (a.cnt_out)
-                    *win::byte_at(a.cnt_out + tbase, ob) = a.max_pts;
+                    gmem(a.cnt_out)[o] = a.max_pts;
                 const float v = (float)((double)z0 + win::quotient64(num, den));
-                *win::byte_at(a.z_out + tbase, ob) = hcnt > 0 ? (float)(hsum / (double)hcnt)
+                gmem(a.z_out)[o] = hcnt > 0 ? (float)(hsum / (double)hcnt)
                                                      : a.max_pts < a.min_pts
                                                          ? NAN
                                                          : fminf(fmaxf(v, lo), hi);

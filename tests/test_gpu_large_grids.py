@@ -1,7 +1,8 @@
 """Calls of 2^32 nodes and more: more node tiles than one launch takes (HIP
 launches fewer than 2^32 threads), as a single grid and as the items of a
-batch.  A few soundings at each grid's corners and centre; every node within
-reach of one is checked against 64-bit arithmetic, and no other has a value."""
+batch; and rows so long that seven of them pass 32-bit byte offsets.  A few
+soundings at each grid's corners and centre; every node within reach of one is
+checked against 64-bit arithmetic, and no other has a value."""
 import numpy as np
 import pytest
 import torch
@@ -83,3 +84,31 @@ def test_batch(cap):
     batch.close()
     for _, z in keep:
         _check(z, nx, ny, r)
+
+
+def test_long_rows():
+    """160M nodes per row at 0.1 mm (6.55 lattice units, not linear): one sounding
+    by the row's end in the first, seventh, eighth and last row."""
+    ag = _ready()
+    nx, ny, dx, dy, r = 160_000_000, 9, 1e-4, 1.0, 0.01
+    rows = [0, 6, 7, 8]
+    x = np.array([15999.0, 15998.0, 15999.99, 15990.0])
+    y = np.array([a + 0.5 + 0.002 for a in rows])
+    d = -np.arange(20.0, 24.0)
+    grid = ag.auv_grid_create(ag.make_desc(0.0, 0.0, dx, dy, nx, ny))
+    bins = ag.auv_bin_points(grid, *(torch.from_numpy(a).cuda() for a in (x, y, d)), r, 20)
+    z = torch.empty((ny, nx), dtype=torch.float32, device="cuda")
+    prm = ag.idw_params(radius=r, min_pts=1, max_pts=0, algo=ag.AUV_ALGO_SPARSE)
+    ag.auv_interp_idw(grid, bins, prm, z)
+    torch.cuda.synchronize()
+    have = 0
+    for xs, ys, a, depth in zip(x, y, rows, d):
+        b = np.arange(max(0, int((xs - r) / dx) - 3), min(nx, int((xs + r) / dx) + 4))
+        ex = np.rint(xs * 65536) - np.rint(((b + 0.5) * dx) * 65536)
+        ey = np.rint(ys * 65536) - np.rint((a + 0.5) * dy * 65536)
+        member = ex * ex + ey * ey <= np.rint(r * 65536) ** 2
+        got = z[a, int(b[0]):int(b[-1]) + 1].cpu().numpy()
+        assert np.array_equal(np.isfinite(got), member)
+        assert (got[member] == np.float32(depth)).all()
+        have += int(member.sum())
+    assert have == sum(int(torch.isfinite(row).sum().item()) for row in z)
