@@ -273,7 +273,7 @@ __global__ __launch_bounds__(kCols) void k_bicubic(const BilArgs p)
 
 // Launch geometry: rows per block and the LDS of the rectangle (`halo` source
 // rows and columns beyond the nodes' extent, slack for the rounding of the axis
-// maps included); 0 bytes: read from memory.  More rows share a block's start,
+// maps included, see axis_maps_fine); 0 bytes: read from memory.  More rows share a block's start,
 // but a small grid needs the blocks (halved, down to 8, while under 2048, eight
 // to a CU), and the rectangle has to fit kStage values, which leave eight
 // blocks to a CU.
@@ -292,7 +292,7 @@ size_t resample_geometry(const auv_grid_desc &s, const auv_grid_desc &d, double 
         n /= 2;
     *rows = n;
     *blocks = (unsigned)(ncb * ((d.ny + n - 1) / n));
-    return rect(n) <= kStage ? sizeof(float) * (size_t)rect(n) : 0;
+    return rect(n) <= kStage && axis_maps_fine(s, d) ? sizeof(float) * (size_t)rect(n) : 0;
 }
 
 BilArgs resample_args(const float *src, const auv_grid_desc &s, float *dst,

@@ -730,8 +730,9 @@ auv_status launch_kriging(const float *src, const auv_grid_desc &s, float *dst,
     // offsets (and a few more at the edges): the form that keeps their weights.
     // Elsewhere every row would compute weights of its own, which costs it as
     // much as a window's product costs the other form, shared by its rows.
-    bool phase = std::fabs(d.dy - s.dy) <= 1e-9 * s.dy ||
-                 std::fabs(2.0 * d.dy - s.dy) <= 1e-9 * s.dy;
+    bool phase = (std::fabs(d.dy - s.dy) <= 1e-9 * s.dy ||
+                  std::fabs(2.0 * d.dy - s.dy) <= 1e-9 * s.dy) &&
+                 axis_maps_fine(s, d);
     // more rows per block reuse more covariance terms or weights, but a small
     // grid needs the blocks: halve (down to 8) while under 1024 blocks
     const int64_t ncb = (d.nx + kKrigCols - 1) / kKrigCols;

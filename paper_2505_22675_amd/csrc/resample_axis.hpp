@@ -32,6 +32,20 @@ __device__ inline Axis axis_of(double x0d, double dd, int j, double x0s, double 
     return a;
 }
 
+// Whether the axis maps' rounding stays below half a source cell, so that a block's
+// source rectangle is known on the host to two cells: no grid of ordinary
+// coordinates fails it, but at origins beyond about 2^49 spacings the nodes step by
+// whole groups of cells.
+inline bool axis_maps_fine(const auv_grid_desc &s, const auv_grid_desc &d)
+{
+    auto fine = [](double s0, double ds, int ns, double d0, double dd, int nd) {
+        // each of the map's five roundings is at most 2^-53 of these
+        const double m = std::fabs(s0) + std::fabs(d0) + ns * ds + nd * dd;
+        return m * 0x1p-50 < 0.5 * ds;
+    };
+    return fine(s.x0, s.dx, s.nx, d.x0, d.dx, d.nx) && fine(s.y0, s.dy, s.ny, d.y0, d.dy, d.ny);
+}
+
 // Copy the source rectangle [jl, jl + sh) x [il, il + sw) into s_dst
 // (row-major, pitch sw) with nthreads threads: element e = t + k nthreads
 // walks (row, column) incrementally, one division per thread in all.
