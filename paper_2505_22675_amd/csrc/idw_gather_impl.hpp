@@ -37,13 +37,11 @@ namespace gather {
 using dense::NodeL;
 using dense::node_lat;
 
-// A staged sounding: lattice offset from the tile's first node (as FP32 where
-// every offset stays below 2^24, else as integer bits), residuals, depth,
-// depth minus the tile's reference, original index.
+// A staged sounding.  p: lattice offset from the tile's first node (as FP32 where
+// every offset stays below 2^24, else as integer bits), residuals.  q: depth,
+// depth minus the tile's reference, original index (bits).
 struct Rec {
-    float4 p;
-    float z, dz;
-    int idx, pad;
+    float4 p, q;
 };
 
 constexpr int kNull = 64;  // the record no node can reach
@@ -52,8 +50,12 @@ constexpr int kNull = 64;  // the record no node can reach
 // its records.
 struct Smem {
     Rec rec[64 + 1];
-    uint16_t list[4][64];
+    alignas(8) uint16_t list[4][64];
 };
+// Two and four list entries at once: types that may alias the entries' own (the
+// lists are written an entry at a time).
+typedef uint32_t __attribute__((may_alias)) Entries2;
+typedef uint32_t __attribute__((ext_vector_type(2), may_alias)) Entries4;
 
 // One instruction each, without the NaN quieting that the compiler adds to
 // fminf / fmaxf of values it cannot prove canonical.
@@ -265,8 +267,7 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
     if (lane == 0) {
         sm.rec[kNull].p = kGen ? make_float4(__int_as_float(1 << 30), __int_as_float(1 << 30), 0.0f, 0.0f)
                                : make_float4(1e19f, 1e19f, 0.0f, 0.0f);
-        *reinterpret_cast<float4 *>(&sm.rec[kNull].z) =
-            make_float4(0.0f, 0.0f, __int_as_float(INT_MAX), 0.0f);
+        sm.rec[kNull].q = make_float4(0.0f, 0.0f, __int_as_float(INT_MAX), 0.0f);
     }
     float zref = 0.0f;
     bool have_ref = false;
@@ -311,12 +312,12 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
         }
         __builtin_amdgcn_wave_barrier();
         const uint32_t nn = kNullOff | (kNullOff << 16);
-        reinterpret_cast<uint2 *>(sm.list)[lane] = make_uint2(nn, nn);
+        reinterpret_cast<Entries4 *>(sm.list)[lane] = Entries4{nn, nn};
         Rec &r = sm.rec[lane];
         r.p = make_float4(kGen ? __int_as_float(xr) : (float)xr, kGen ? __int_as_float(yr) : (float)yr,
                           (float)(int16_t)(res & 0xffffu) * kResidualUnit,
                           (float)(int16_t)(res >> 16) * kResidualUnit);
-        *reinterpret_cast<float4 *>(&r.z) = make_float4(z, z - zref, __int_as_float(idx), 0.0f);
+        r.q = make_float4(z, z - zref, __int_as_float(idx), 0.0f);
         int n = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -352,7 +353,7 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
         // bits of D2 + 2^52: the integer D2 under an exponent that the shift by at
         // least 12 drops; 2^52 added to the key makes it a normal number
         const unsigned long long key =
-            (((unsigned long long)__double_as_longlong(D2 + 0x1p52)) << kb) | (unsigned)r->idx;
+            (((unsigned long long)__double_as_longlong(D2 + 0x1p52)) << kb) | __float_as_uint(r->q.z);
         const double v = __longlong_as_double((long long)(key + (1ull << 52)));
         return (D2 <= R2) & (v > last) ? v : __builtin_huge_val();
     };
@@ -364,7 +365,7 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
         each([&](int n) {
 #pragma unroll 1
             for (int e = 0; e < n; e += 4) {
-                const uint2 o = *reinterpret_cast<const uint2 *>(lst + e);
+                const Entries4 o = *reinterpret_cast<const Entries4 *>(lst + e);
                 dense::merge4(list, entry(o.x & 0xffffu, 0.0), entry(o.x >> 16, 0.0),
                               entry(o.y & 0xffffu, 0.0), entry(o.y >> 16, 0.0));
             }
@@ -379,13 +380,13 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
         // two records at a time (their reads overlap)
 #pragma unroll 1
         for (int e = 0; e < n; e += 2) {
-            const uint32_t o2 = *reinterpret_cast<const uint32_t *>(lst + e);
+            const uint32_t o2 = *reinterpret_cast<const Entries2 *>(lst + e);
             const Rec *const rp[2] = {rec_at(o2 & 0xffffu), rec_at(o2 >> 16)};
             float4 p[2], q[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 p[u] = rp[u]->p;
-                q[u] = *reinterpret_cast<const float4 *>(&rp[u]->z);
+                q[u] = rp[u]->q;
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -451,7 +452,7 @@ __device__ __forceinline__ void gather_tile(const auv_bin_view &bv, const IdwArg
                 for (int e = 0; e < n; ++e) {
                     const Rec *r = rec_at(lst[e]);
                     const bool h = off_x(r->p) == 0 && off_y(r->p) == 0;
-                    hsum += h ? (double)r->z : 0.0;
+                    hsum += h ? (double)r->q.x : 0.0;
                     hcnt += h ? 1 : 0;
                 }
             });
