@@ -216,8 +216,14 @@ __global__ __launch_bounds__(kVThreads, 4) void k_vario_partial(const float *__r
             }
         }
     }
+    // a thread's pairs fit 32 bits (a 256th of a block's columns times its rows),
+    // a wave's of a grid of 1e9 columns do not
+    long long cl[kVLags];
+#pragma unroll
+    for (int l = 0; l < kVLags; ++l)
+        cl[l] = c[l];
     const double sum = wave_sums(s);
-    const int cnt = wave_sums(c);
+    const long long cnt = wave_sums(cl);
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if ((lane & 7) == 0)
         s_sum[w][lane >> 3] = VPart{sum, cnt};
