@@ -1,7 +1,8 @@
 // Empirical semivariogram of a grid along its axes, and the exponential
 // variogram fit that gives kriging (Sec. III-C) its range.
 //
-//   k_vario_partial  one block per (axis, group of kVLags lags, band of rows):
+//   k_vario_partial  one block per (axis, group of kVLags lags, band of rows or
+//                    piece of one):
 //                    FP64 sums of the squared differences of the pairs at
 //                    those lags with both values finite, and their counts
 //   k_vario_final    one block per (axis, lag): the bands' partials summed in
@@ -123,8 +124,9 @@ __device__ __forceinline__ T wave_sums(T (&v)[kVLags])
     return r;
 }
 
-// grid: (bands, ceil(nlags / kVLags), 2 axes).  Band b takes rows
-// [b * rows, (b + 1) * rows).
+// grid: (bands * splits, ceil(nlags / kVLags), 2 axes).  Band b takes the pairs
+// whose first value lies in rows [b * rows, (b + 1) * rows); block b * splits + i of
+// them takes the first values of columns [i * cols, (i + 1) * cols) (see splits_for).
 //
 // Bound by FP64 instruction issue: about 4.8 instructions per pair (three of
 // them FP64), each value read once per eight lags instead of once per pair.
@@ -135,12 +137,14 @@ __device__ __forceinline__ T wave_sums(T (&v)[kVLags])
 // per two loads, counts by compare: 107 us).
 __global__ __launch_bounds__(kVThreads, 4) void k_vario_partial(const float *__restrict__ src,
                                                              int nx, int ny, int nlags, int rows,
+                                                             int cols, int splits,
                                                              VPart *__restrict__ part)
 {
     __shared__ float s_a[kVThreads * 9], s_b[(kVThreads + kVRowsMax) * 9];
     __shared__ VPart s_sum[kVThreads / 64][kVLags];
-    const int bands = gridDim.x, band = blockIdx.x, axis = blockIdx.z;
+    const int band = blockIdx.x / splits, axis = blockIdx.z;
     const int k0 = blockIdx.y * kVLags;  // lags k0 + 1 .. k0 + kVLags
+    const int cb = ((int)blockIdx.x - band * splits) * cols, ce = min(nx, cb + cols);
     const int r0 = band * rows, r1 = min(ny, r0 + rows);
     double s[kVLags];
     int c[kVLags];
@@ -152,24 +156,24 @@ __global__ __launch_bounds__(kVThreads, 4) void k_vario_partial(const float *__r
     float za[kVRun], zb[kVWin];
     if (axis == 0) {
         // runs per row (at most a block's threads), rows per pass
-        const int nch = min(kVThreads, (nx + kVRun - 1) / kVRun);
+        const int nch = min(kVThreads, (ce - cb + kVRun - 1) / kVRun);
         const int per = min(kVRowsMax, kVThreads / nch);
         const int rl = threadIdx.x / nch, ch = threadIdx.x - rl * nch;
         float *const pa = s_a + rl * nch * 9, *const pb = s_b + rl * (nch + 1) * 9;
-        for (int c0 = 0; c0 < nx - 1 - k0; c0 += nch * kVRun) {
+        for (int c0 = cb; c0 < min(ce, nx - 1 - k0); c0 += nch * kVRun) {
             for (int a = r0; a < r1; a += per) {
                 // loads beyond the grid read its last row or column instead
                 const bool on = rl < per && a + rl < r1;
                 const float *const row = src + (size_t)min(a + rl, ny - 1) * nx;
-                auto load = [&](int b) {
+                auto load = [&](int b, int end) {
                     const float z = finite_or_nan(row[min(b, nx - 1)]);
-                    return on && b < nx ? z : NAN;
+                    return on && b < end ? z : NAN;
                 };
                 float va[kVRun], vb[kVRun];
 #pragma unroll
                 for (int j = 0; j < kVRun; ++j) {
-                    va[j] = load(c0 + j * nch + ch);
-                    vb[j] = load(c0 + 1 + k0 + j * nch + ch);
+                    va[j] = load(c0 + j * nch + ch, ce);
+                    vb[j] = load(c0 + 1 + k0 + j * nch + ch, nx);
                 }
                 __syncthreads();  // the previous pass is read
                 if (rl < per) {
@@ -180,7 +184,7 @@ __global__ __launch_bounds__(kVThreads, 4) void k_vario_partial(const float *__r
                         pb[p + (p >> 3)] = vb[j];
                     }
                     for (int p = nch * kVRun + ch; p < (nch + 1) * kVRun; p += nch)
-                        pb[p + (p >> 3)] = load(c0 + 1 + k0 + p);
+                        pb[p + (p >> 3)] = load(c0 + 1 + k0 + p, nx);
                 }
                 __syncthreads();
                 if (on) {
@@ -195,7 +199,7 @@ __global__ __launch_bounds__(kVThreads, 4) void k_vario_partial(const float *__r
             }
         }
     } else {
-        for (int b = threadIdx.x; b < nx; b += kVThreads) {
+        for (int b = cb + (int)threadIdx.x; b < ce; b += kVThreads) {
             for (int a0 = r0; a0 < min(r1, ny - 1 - k0); a0 += kVRun) {
                 // opaque: the rows' addresses and tests are not worth the
                 // registers it takes to keep them from one b to the next
@@ -235,7 +239,7 @@ __global__ __launch_bounds__(kVThreads, 4) void k_vario_partial(const float *__r
             t.sum += s_sum[i][l].sum;
             t.cnt += s_sum[i][l].cnt;
         }
-        part[((size_t)axis * nlags + k0 + l) * bands + band] = t;
+        part[((size_t)axis * nlags + k0 + l) * gridDim.x + blockIdx.x] = t;
     }
 }
 
@@ -264,6 +268,17 @@ int band_rows(int ny)
     return (r + kVRun - 1) / kVRun * kVRun;
 }
 int bands_for(int ny) { return std::max(1, std::min(ny, kMaxBands)); }  // workspace
+
+// Column pieces of a band: few bands leave CUs idle (one block of a wide grid of
+// eight rows walked all its columns: 1e6 x 8 nodes, 64 lags, 6.97 ms, before the
+// runs of eight 2.14 ms), so they are split while the launch has under 1024 blocks,
+// into pieces of at least 64 columns and as far as the workspace holds partials.
+int splits_for(int nx, int ny, int nlags, int bands)
+{
+    const int groups = (nlags + kVLags - 1) / kVLags;
+    const int want = (1024 + 2 * groups * bands - 1) / (2 * groups * bands);
+    return std::max(1, std::min({want, nx / 64, bands_for(ny) / bands}));
+}
 
 size_t vario_ws_bytes(int ny, int nlags)
 {
@@ -343,13 +358,16 @@ auv_status auv_variogram(const float *src, const auv_grid_desc *s, int32_t nlags
         return fail(AUV_ERR_INVALID, "workspace must be 256-byte aligned");
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int rows = band_rows(s->ny), bands = (s->ny + rows - 1) / rows;
+    const int splits = splits_for(s->nx, s->ny, nlags, bands);
+    const int cols = (s->nx + splits - 1) / splits;  // (every piece has some)
+    const int pieces = bands * splits;
     VPart *part = static_cast<VPart *>(ws);
-    const size_t parts = (size_t)2 * nlags * bands * sizeof(VPart);
+    const size_t parts = (size_t)2 * nlags * pieces * sizeof(VPart);
     VPart *out = reinterpret_cast<VPart *>(static_cast<char *>(ws) + ((parts + 255) & ~size_t(255)));
     const unsigned groups = (unsigned)((nlags + kVLags - 1) / kVLags);
-    k_vario_partial<<<dim3((unsigned)bands, groups, 2), kVThreads, 0, hs>>>(src, s->nx, s->ny,
-                                                                           nlags, rows, part);
-    k_vario_final<<<(unsigned)(2 * nlags), kVThreads, 0, hs>>>(part, bands, out);
+    k_vario_partial<<<dim3((unsigned)pieces, groups, 2), kVThreads, 0, hs>>>(
+        src, s->nx, s->ny, nlags, rows, cols, splits, part);
+    k_vario_final<<<(unsigned)(2 * nlags), kVThreads, 0, hs>>>(part, pieces, out);
     AUV_HIP(hipGetLastError());
     std::vector<VPart> host(2 * (size_t)nlags);
     AUV_HIP(hipMemcpyAsync(host.data(), out, sizeof(VPart) * host.size(), hipMemcpyDeviceToHost,
