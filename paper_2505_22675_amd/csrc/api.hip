@@ -301,6 +301,7 @@ auv_status auv_interp_idw(const auv_grid *grid, const auv_bins *bins,
         const double r = params->radius;
         const double area = (grid->d.nx * grid->d.dx + 2 * r) * (grid->d.ny * grid->d.dy + 2 * r);
         const double lambda = (double)bins->n / area * 3.141592653589793 * r * r;
+        a.population = (float)lambda;
         const bool dense_ok = params->max_pts >= 1 && params->max_pts <= 32 &&
                               params->precision == AUV_P_FP32_REBASE &&
                               dense::dense_key_ok(a.R, bins->v.idx_bits);

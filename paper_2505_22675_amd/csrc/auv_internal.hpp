@@ -206,7 +206,8 @@ struct IdwArgs {
     int32_t R_stage;          // lattice reach of the candidate search (>= R)
     float r2f;                // radius^2 in m^2, FP32 (precision variants)
     double x0, y0;            // grid origin (precision variants)
-    bool dense;               // use the dense (ring search, top-k) form
+    float population;         // expected soundings per disk (dense: which search)
+    bool dense;               // use the dense (top-k) form
     bool span;                // sparse: the span form where it applies
     int32_t pmode;            // 1, 2, 3: integer power (fast weights), 0: general
     int32_t tile_w, tile_h;   // nodes per wave tile (0: the form's default): window
@@ -241,8 +242,10 @@ bool gather_covers(const auv_bin_view &bv, const IdwArgs &a);
 auv_status launch_idw_gather(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g,
                              hipStream_t st);
 // The dense form by the gather form's lists: whether it covers a call (bins of at
-// least the radius), and its launch.
+// least the radius), whether a single call is faster by it than by the ring search,
+// and its launch.
 bool gather_top_covers(const auv_bin_view &bv, const IdwArgs &a);
+bool gather_top_pays(const IdwArgs &a);
 auv_status launch_idw_gather_top(const auv_bin_view &bv, const IdwArgs &a, const WinGeom *g,
                                  hipStream_t st);
 auv_status launch_idw_dense(const auv_bin_view &bins, const IdwArgs &a, int pmode,

@@ -402,6 +402,7 @@ void item_views(const auv_batch *b, int i, char *ws, const BinGeom &geom, int32_
     x.cnt_out = it.cnt_out;
     x.nn_idx_out = it.nn_idx_out;
     x.nn_z_out = it.nn_z_out;
+    x.population = (float)disk_population(it);
     x.dense = algo == AUV_ALGO_DENSE;
     x.span = algo == AUV_ALGO_SPAN;
     x.pmode = pmode_of(it.params.power);

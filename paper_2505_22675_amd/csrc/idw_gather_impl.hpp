@@ -565,7 +565,7 @@ __global__ __launch_bounds__(64, 8) void k_idw_gather(auv_bin_view bv, IdwArgs a
 }
 
 // Waves per SIMD that the list leaves room for.
-constexpr int top_waves(int top) { return top == 8 ? 8 : top == 16 ? 5 : 3; }
+constexpr int top_waves(int top) { return top == 8 ? 8 : 5; }
 
 // The dense form on bins of at least the radius.  Its ring search reads nine
 // such bins per node whatever the density, five times the disk; the quarters'
@@ -573,7 +573,8 @@ constexpr int top_waves(int top) { return top == 8 ? 8 : top == 16 ? 5 : 3; }
 // of once per node.  Bound by vector instruction issue (the list merges) and, at
 // one wave generation, by the chain of a tile's batches.  512^2 nodes, disks of
 // (cap): 20 (16) 50 -> 46 us, 9 (16) 31 -> 26, 30 (16) 68 -> 59, 5 (8) 23 -> 14, 20 (8)
-// 47 -> 31, 25 (24) 91 -> 83; finer bins keep the ring search (it stops after a few).
+// 47 -> 31; finer bins, caps above 16 and dense disks keep the ring search
+// (gather_top_pays).
 template <int kMode, int kTop, bool kGen>
 __global__ __launch_bounds__(64, top_waves(kTop)) void k_idw_gather_top(auv_bin_view bv, IdwArgs a,
                                                                       WinGeom g, int ntx,

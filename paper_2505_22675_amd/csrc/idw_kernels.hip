@@ -373,9 +373,10 @@ auv_status launch_idw(const auv_bin_view &bv, const IdwArgs &a_in, hipStream_t s
     a.pmode = pmode;
     WinGeom wg;
     const bool linear = window_geometry(a, &wg);
-    // The dense form: by the gather form's lists on bins of at least the radius,
-    // by its ring search on finer ones, where it stops after a few small bins.
-    if (a.dense && gather_top_covers(bv, a))
+    // The dense form: by the gather form's lists on bins of at least the radius and
+    // up to some density, by its ring search on finer bins, where it stops after a
+    // few small ones, and at higher densities.
+    if (a.dense && gather_top_covers(bv, a) && gather_top_pays(a))
         return launch_idw_gather_top(bv, a, linear ? &wg : nullptr, st);
     if (a.dense)
         return launch_idw_dense(bv, a, pmode, st);
