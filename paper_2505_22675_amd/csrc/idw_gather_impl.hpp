@@ -106,12 +106,17 @@ __device__ __forceinline__ void add_weight(const IdwArgs &a, float d2, float dz,
 
 // The binned positions of the bin rows and columns that meet a box, 64 at a
 // time (one per lane): the rows' ranges are filled into the lanes one after
-// the other.
+// the other, empty rows skipped by a mask (small radii have dozens of bin rows
+// per tile, most of them empty).  Against a walk over every row: radius a tenth of
+// the spacing, 100k soundings on 1000^2 nodes 44 -> 24 us (the window form 24); and
+// with fewer branches between a row and the next, the 2M-sounding step 291 -> 270 us,
+// the 256-tile batch 1740 -> 1628.
 struct Batches {
     const auv_bin_view &bv;
     int by_lo, nrows, bx_lo, nbx_row;
-    int rb, nr, r, pos, lim;  // row block, rows in it, current row and its rest
-    int beg, end;             // this lane's row
+    int rb, pos, lim;          // row block; the rest of the current row
+    unsigned long long rows;   // non-empty rows of the block not yet begun
+    int beg, end;              // this lane's row
 
     // lattice box [x0, x1] x [y0, y1] (nodes), grown by R
     __device__ __forceinline__ Batches(const auv_bin_view &v, int R, int x0, int x1, int y0, int y1)
@@ -129,16 +134,13 @@ struct Batches {
     {
         const int lane = threadIdx.x & 63;
         const auto cs = gmem(bv.cell_start);
-        nr = min(64, nrows - rb);
-        beg = end = 0;
-        if (lane < nr) {
-            const int id0 = (by_lo + rb + lane) * bv.nbx + bx_lo;
-            beg = cs[id0];
-            end = cs[id0 + nbx_row];
-        }
-        r = 0;
-        pos = __builtin_amdgcn_readlane(beg, 0);
-        lim = __builtin_amdgcn_readlane(end, 0);
+        // lanes past the last row repeat it
+        const int left = nrows - rb;
+        const int id0 = (by_lo + rb + min(lane, left - 1)) * bv.nbx + bx_lo;
+        beg = cs[id0];
+        end = cs[id0 + nbx_row];
+        rows = __ballot(end > beg) & (~0ull >> (64 - min(left, 64)));
+        pos = lim = 0;
     }
     // The next batch: this lane's position k, valid for lanes below the
     // returned count (0: no batch is left).
@@ -146,31 +148,27 @@ struct Batches {
     {
         const int lane = threadIdx.x & 63;
         int filled = 0, kk = 0;
-        while (filled < 64) {
+        do {
             if (pos == lim) {
-                if (++r >= nr) {
-                    if (rb + 64 >= nrows || filled > 0) {
-                        r = nr;
-                        break;
-                    }
+                while (rows == 0ull && filled == 0 && rb + 64 < nrows) {
                     rb += 64;
                     load();
-                    continue;
                 }
+                if (rows == 0ull)
+                    break;
+                const int r = __ffsll((long long)rows) - 1;
+                rows &= rows - 1ull;
                 pos = __builtin_amdgcn_readlane(beg, r);
                 lim = __builtin_amdgcn_readlane(end, r);
-                continue;
             }
             kk = lane >= filled ? pos + (lane - filled) : kk;
             const int take = min(64 - filled, lim - pos);
             filled += take;
             pos += take;
-        }
+        } while (filled < 64);
         *k = kk;
         return filled;
     }
-    // whether the batches so far were all
-    __device__ __forceinline__ bool done() const { return r >= nr && rb + 64 >= nrows; }
 };
 
 // kGen: any node lattice and any radius (nodes with residuals, offsets of any
