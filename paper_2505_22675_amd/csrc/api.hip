@@ -235,6 +235,14 @@ auv_status auv_bins_export(const auv_bins *bins, int32_t *cell_start, int32_t *p
 
 void auv_bins_destroy(auv_bins *bins) { delete bins; }
 
+// Expected soundings per disk, from the input count over the grid grown by the
+// radius.
+static double expected_population(const auv_grid *g, const auv_bins *bins, double r)
+{
+    const double area = (g->d.nx * g->d.dx + 2 * r) * (g->d.ny * g->d.dy + 2 * r);
+    return (double)bins->n / area * 3.141592653589793 * r * r;
+}
+
 static auv_status idw_common(const auv_grid *grid, const auv_bins *bins,
                              double radius, IdwArgs *a)
 {
@@ -255,6 +263,7 @@ static auv_status idw_common(const auv_grid *grid, const auv_bins *bins,
     a->R = (int32_t)Rd;
     a->R_stage = (int32_t)Rd;
     a->inv_r2 = (float)(1.0 / (Rd * Rd));
+    a->population = (float)expected_population(grid, bins, radius);
     a->r2f = (float)(radius * radius);
     a->x0 = grid->d.x0;
     a->y0 = grid->d.y0;
@@ -296,12 +305,7 @@ auv_status auv_interp_idw(const auv_grid *grid, const auv_bins *bins,
     a.precision = params->precision;
     a.mode = (nn_idx_out || nn_z_out) ? 3 : 1;
     {
-        // expected soundings per disk, from the input count over the grid
-        // grown by the radius
-        const double r = params->radius;
-        const double area = (grid->d.nx * grid->d.dx + 2 * r) * (grid->d.ny * grid->d.dy + 2 * r);
-        const double lambda = (double)bins->n / area * 3.141592653589793 * r * r;
-        a.population = (float)lambda;
+        const double lambda = expected_population(grid, bins, params->radius);
         const bool dense_ok = params->max_pts >= 1 && params->max_pts <= 32 &&
                               params->precision == AUV_P_FP32_REBASE &&
                               dense::dense_key_ok(a.R, bins->v.idx_bits);

@@ -206,7 +206,7 @@ struct IdwArgs {
     int32_t R_stage;          // lattice reach of the candidate search (>= R)
     float r2f;                // radius^2 in m^2, FP32 (precision variants)
     double x0, y0;            // grid origin (precision variants)
-    float population;         // expected soundings per disk (dense: which search)
+    float population;         // expected soundings per disk (which form is faster)
     bool dense;               // use the dense (top-k) form
     bool span;                // sparse: the span form where it applies
     int32_t pmode;            // 1, 2, 3: integer power (fast weights), 0: general

@@ -356,6 +356,36 @@ __global__ __launch_bounds__(64) void k_idw_tile(auv_bin_view bv, IdwArgs a,
 
 }  // namespace
 
+namespace {
+
+// Whether the window form is faster than the gather form on a linear lattice
+// (without a cap: the window form finishes nodes above one at a time, a hundred
+// times slower where soundings cluster).
+//
+// Many almost empty tiles: the window form's cover four times the nodes, and a
+// wave's chain of waits is all that such a tile costs.  Nearest pick at 0.1, 0.3, 1
+// and 4 soundings per disk of 3 spacings, spread evenly, gather / window: 4096^2
+// nodes 71 / 54, 88 / 64, 120 / 97, 271 / 398 us, 2048^2 21 / 16, 25 / 18, 35 / 29,
+// 77 / 117, 1024^2 8 / 7, 9 / 7, 12 / 10, 24 / 33; gathered in stripes on a tenth
+// of the grid, 4096^2 77 / 46, 81 / 61, 99 / 114 at 0.1, 0.3 and 1, 2048^2 25 / 19,
+// 27 / 28, 33 / 57.  The bound, four soundings expected within reach of an 8 x 8
+// tile, is 0.6 per disk there; up to 1.7 per disk evenly spread soundings would
+// be a little faster by windows, clustered ones half as fast.
+//
+// More than 64 bin rows per tile: the gather form reads them 64 at a time, each a
+// wait of its own (1000^2 nodes at 16 m, radius 0.32 m, 100k soundings 171 / 95 us).
+bool window_pays(const auv_bin_view &bv, const IdwArgs &a, const WinGeom &g)
+{
+    if (a.max_pts > 0 && a.mode != 2)
+        return false;
+    const double R = a.R, per_unit2 = a.population / (3.141592653589793 * R * R);
+    const double reach = per_unit2 * (8.0 * g.DXl + 2.0 * R) * (8.0 * g.DYl + 2.0 * R);
+    const int64_t rows = ((7 * (int64_t)g.DYl + 2 * (int64_t)a.R) >> bv.bin_log2) + 2;
+    return rows > 64 || (reach <= 4.0 && (int64_t)a.nx * a.ny >= 32768 * 64);
+}
+
+}  // namespace
+
 auv_status launch_idw(const auv_bin_view &bv, const IdwArgs &a_in, hipStream_t st)
 {
     IdwArgs a = a_in;
@@ -380,10 +410,11 @@ auv_status launch_idw(const auv_bin_view &bv, const IdwArgs &a_in, hipStream_t s
         return launch_idw_gather_top(bv, a, linear ? &wg : nullptr, st);
     if (a.dense)
         return launch_idw_dense(bv, a, pmode, st);
-    // The gather form takes every exact call that it covers: at 20k to 2M
-    // soundings it was measured faster than the window form on linear lattices
-    // (1.02 to 1.9 times) and than the tile kernel on the others (1.9 times).
-    if (!a.span && gather_covers(bv, a))
+    // The gather form takes every exact call that it covers, but for a few on
+    // linear lattices: at 20k to 2M soundings it was measured faster than the window
+    // form there (1.02 to 1.9 times) and than the tile kernel on the others (1.9
+    // times).
+    if (!a.span && gather_covers(bv, a) && !(linear && window_pays(bv, a, wg)))
         return launch_idw_gather(bv, a, linear ? &wg : nullptr, st);
     if (linear)
         return launch_idw_window(bv, a, wg, pmode, st);
