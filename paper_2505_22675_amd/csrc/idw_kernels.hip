@@ -403,6 +403,8 @@ auv_status launch_idw(const auv_bin_view &bv, const IdwArgs &a_in, hipStream_t s
     a.pmode = pmode;
     WinGeom wg;
     const bool linear = window_geometry(a, &wg);
+    // the window form addresses a tile's 16 rows by 32-bit byte offsets
+    const bool window = linear && a.nx <= 1 << 26;
     // The dense form: by the gather form's lists on bins of at least the radius and
     // up to some density, by its ring search on finer bins, where it stops after a
     // few small ones, and at higher densities.
@@ -414,9 +416,9 @@ auv_status launch_idw(const auv_bin_view &bv, const IdwArgs &a_in, hipStream_t s
     // linear lattices: at 20k to 2M soundings it was measured faster than the window
     // form there (1.02 to 1.9 times) and than the tile kernel on the others (1.9
     // times).
-    if (!a.span && gather_covers(bv, a) && !(linear && window_pays(bv, a, wg)))
+    if (!a.span && gather_covers(bv, a) && !(window && window_pays(bv, a, wg)))
         return launch_idw_gather(bv, a, linear ? &wg : nullptr, st);
-    if (linear)
+    if (window || (linear && a.precision != AUV_P_FP32_REBASE))
         return launch_idw_window(bv, a, wg, pmode, st);
     if (a.precision != AUV_P_FP32_REBASE)
         return fail(AUV_ERR_INVALID,

@@ -86,19 +86,24 @@ def test_batch(cap):
         _check(z, nx, ny, r)
 
 
-def test_long_rows():
-    """160M nodes per row at 0.1 mm (6.55 lattice units, not linear): one sounding
-    by the row's end in the first, seventh, eighth and last row."""
+@pytest.mark.parametrize("nx,dx,cap", [
+    (160_000_000, 1e-4, 0),            # 6.55 lattice units: not linear
+    (130_000_000, 2.0 ** -13, 0),      # linear
+    (130_000_000, 2.0 ** -13, 70),     # beyond the gather form's caps
+])
+def test_long_rows(nx, dx, cap):
+    """One sounding by the row's end in the first, seventh, eighth and last row."""
     ag = _ready()
-    nx, ny, dx, dy, r = 160_000_000, 9, 1e-4, 1.0, 0.01
+    ny, dy, r = 9, 1.0, 0.01
+    end = nx * dx
     rows = [0, 6, 7, 8]
-    x = np.array([15999.0, 15998.0, 15999.99, 15990.0])
+    x = np.array([end - 1.0, end - 2.0, end - 0.01, end - 10.0])
     y = np.array([a + 0.5 + 0.002 for a in rows])
     d = -np.arange(20.0, 24.0)
     grid = ag.auv_grid_create(ag.make_desc(0.0, 0.0, dx, dy, nx, ny))
     bins = ag.auv_bin_points(grid, *(torch.from_numpy(a).cuda() for a in (x, y, d)), r, 20)
     z = torch.empty((ny, nx), dtype=torch.float32, device="cuda")
-    prm = ag.idw_params(radius=r, min_pts=1, max_pts=0, algo=ag.AUV_ALGO_SPARSE)
+    prm = ag.idw_params(radius=r, min_pts=1, max_pts=cap, algo=ag.AUV_ALGO_SPARSE)
     ag.auv_interp_idw(grid, bins, prm, z)
     torch.cuda.synchronize()
     have = 0
