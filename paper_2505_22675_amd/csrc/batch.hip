@@ -36,18 +36,20 @@ namespace {
 
 constexpr int kXcds = 8;
 constexpr int kRun = 64;  // consecutive units of one XCD
-constexpr int kForms = 4; // sparse, dense, span, top
+constexpr int kForms = 6;
 constexpr int kFewSortRows = 2560;  // ten bin rows per CU
 constexpr int kBatchDenseK = 16;  // largest max_pts the batched dense kernel keeps
 
-enum { kSparse = 0, kDense = 1, kSpan = 2, kTop = 3 };
+// gather form on linear lattices, dense ring search, span, dense by lists, gather form
+// on any lattice, window form
+enum { kSparse = 0, kDense = 1, kSpan = 2, kTop = 3, kWide = 4, kWindow = 5 };
 
 struct IdwItem {
     auv_bin_view bv;
     IdwArgs a;
     WinGeom g;
     int32_t ntx, ntiles;
-    int32_t form, pmode;  // form: kSparse, kDense (ring search), kSpan or kTop (dense by lists)
+    int32_t form, pmode;
 };
 
 // The unit of block b out of n: blocks are dealt round-robin to the 8 XCDs,
@@ -72,7 +74,7 @@ __device__ inline int deal_unit(int b, int n)
 // queues): 32 tiles of 512^2 nodes with 0.25 / 2 / 8 soundings per disk, binning
 // included, 699 / 716 / 912 -> 136 / 185 / 572 us (cap 16), 877 -> 385 us
 // (8 per disk, no cap).
-template <bool kGeneral>
+template <bool kGeneral, bool kGen>
 __global__ __launch_bounds__(256, 8) void k_idw_batch_sparse(const IdwItem *__restrict__ items,
                                                              const int2 *__restrict__ work, int n,
                                                              int b0)
@@ -89,14 +91,43 @@ __global__ __launch_bounds__(256, 8) void k_idw_batch_sparse(const IdwItem *__re
     // an instantiation per integer power (a test of the power at every visit
     // costs a tenth) and one for a general power, with its rescaled sums
     if (it.pmode == 2) {
-        gather::gather_tile<3, 2, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
+        gather::gather_tile<3, 2, kGen>(it.bv, it.a, it.g, tx, ty, sm[wave]);
     } else if (it.pmode == 1) {
-        gather::gather_tile<3, 1, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
+        gather::gather_tile<3, 1, kGen>(it.bv, it.a, it.g, tx, ty, sm[wave]);
     } else if (it.pmode == 3) {
-        gather::gather_tile<3, 3, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
+        gather::gather_tile<3, 3, kGen>(it.bv, it.a, it.g, tx, ty, sm[wave]);
     } else if constexpr (kGeneral) {
-        gather::gather_tile<3, 0, false>(it.bv, it.a, it.g, tx, ty, sm[wave]);
+        gather::gather_tile<3, 0, kGen>(it.bv, it.a, it.g, tx, ty, sm[wave]);
     }
+}
+
+// Window: caps and keys beyond the gather form's, one 16 x 16 or 16 x 8 node tile per
+// block.  Integer powers share one instantiation (the power at run time).  One launch
+// per item instead, in series: 200 tiles of 64^2 nodes, cap 100, 2 / 12 / 40
+// soundings per disk 2.1 / 8.1 / 24.5 ms.
+template <bool kGeneral>
+__global__ __launch_bounds__(64) void k_idw_batch_window(const IdwItem *__restrict__ items,
+                                                         const int2 *__restrict__ work, int n,
+                                                         int b0)
+{
+    __shared__ float2 s_nd[win::kAcc];
+    __shared__ int s_cnt[win::kAcc];
+    __shared__ float s_lo[win::kAcc], s_hi[win::kAcc];
+    __shared__ unsigned long long s_key[win::kAcc];
+    __shared__ float s_emax[kGeneral ? win::kAcc : 1];
+    __shared__ int s_beg[win::kMaxRows], s_off[win::kMaxRows + 1];
+    __shared__ int4 s_rec[win::kRecSlots];
+    const win::WinSmem sm{s_nd, s_cnt, s_lo, s_hi, s_key, nullptr, nullptr, nullptr,
+                          s_emax, s_beg, s_off, s_rec, s_rec + 1, nullptr};
+    const int2 w = work[deal_unit(b0 + (int)blockIdx.x, n)];
+    const IdwItem &it = items[w.x];
+    if constexpr (kGeneral) {
+        if (it.pmode == 0) {
+            win::window_tile<3, 0, true, 1, AUV_P_FP32_REBASE>(it.bv, it.a, it.g, w.y, it.ntx, sm);
+            return;
+        }
+    }
+    win::window_tile<3, -1, true, 1, AUV_P_FP32_REBASE>(it.bv, it.a, it.g, w.y, it.ntx, sm);
 }
 
 // Dense: one node tile of 64 nodes per block.
@@ -149,10 +180,12 @@ void launch_form(int form, bool general, const IdwItem *items, const int2 *work,
         pieces(k_idw_batch_top, 64);
     else if (form == kSpan)
         pieces(k_idw_batch_span, 64);
-    else if (general)
-        pieces(k_idw_batch_sparse<true>, 256);
+    else if (form == kWindow)
+        pieces(general ? k_idw_batch_window<true> : k_idw_batch_window<false>, 64);
+    else if (form == kWide)
+        pieces(general ? k_idw_batch_sparse<true, true> : k_idw_batch_sparse<false, true>, 256);
     else
-        pieces(k_idw_batch_sparse<false>, 256);
+        pieces(general ? k_idw_batch_sparse<true, false> : k_idw_batch_sparse<false, false>, 256);
 }
 
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -323,7 +356,7 @@ struct auv_batch {
     int32_t hist_blocks = 0, scatter_blocks = 0, nrow_items = 0;
     auv::RowSortClass sort_class[auv::kRowSortClasses];
     int32_t work_off[auv::kForms + 1] = {0};  // each form's units in `work`
-    bool any_general = false;  // a sparse item with a general power
+    bool any_general[auv::kForms] = {};  // the form has an item with a general power
     int32_t max_nbx = 0, max_nby = 0;  // largest bin domain of the row-binned items
     hipStream_t cap_stream2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -447,7 +480,8 @@ std::map<ClassKey, Choice> read_tune(const char *path)
 }
 
 // The batched kernels' descriptor of one item; false when they do not cover it
-// (a node lattice that is not linear, a cap above the forms' limits).
+// (dense caps above 16; caps above 64 on lattices that are not linear or with windows
+// of several chunks).
 bool make_idw_item(const auv_batch_item &it, const auv_bin_view &bv, const IdwArgs &a,
                    int32_t algo, IdwItem *out)
 {
@@ -468,10 +502,18 @@ bool make_idw_item(const auv_batch_item &it, const auv_bin_view &bv, const IdwAr
         d.ntx = (it.grid.nx + tw - 1) / tw;
         d.ntiles = d.ntx * ((it.grid.ny + th - 1) / th);
     } else {
-        ok = window_geometry(a, &d.g);
-        d.form = ok && a.span && span::span_ok(bv, a, d.g, d.pmode) ? kSpan : kSparse;
-        ok = ok && (d.form == kSpan || (gather::gather_linear(d.g, a.R) &&
-                                        gather::gather_ok(a.R, bv.idx_bits, it.params.max_pts)));
+        const bool linear = window_geometry(a, &d.g);
+        if (linear && a.span && span::span_ok(bv, a, d.g, d.pmode)) {
+            d.form = kSpan;
+        } else if (gather::gather_ok(a.R, bv.idx_bits, it.params.max_pts)) {
+            d.form = linear && gather::gather_linear(d.g, a.R) ? kSparse : kWide;
+        } else {
+            // windows of one chunk, keys (D^2 << index bits | index) of 64 bits
+            d.form = kWindow;
+            ok = linear && d.g.nchunks == 1 && it.grid.nx <= 1 << 26 &&
+                 ((unsigned __int128)((unsigned long long)a.R * a.R) << bv.idx_bits) <
+                     ((unsigned __int128)1 << 64);
+        }
         const int th = d.form == kSpan ? win::kTH : win::tile_rows(a);
         d.ntx = (it.grid.nx + win::kTW - 1) / win::kTW;
         d.ntiles = d.ntx * ((it.grid.ny + th - 1) / th);
@@ -563,14 +605,14 @@ auv_status build_tables(auv_batch *b, char *ws)
     std::stable_sort(order.begin(), order.end(),
                      [&](int x, int y) { return tile_cost[x] > tile_cost[y]; });
     b->work.clear();
-    b->any_general = false;
     for (int form = 0; form < kForms; ++form) {
+        b->any_general[form] = false;
         for (int i : order) {
             if (!b->covered[i] || b->idw[i].form != form)
                 continue;
             for (int t = 0; t < b->idw[i].ntiles; ++t)
                 b->work.push_back(make_int2(i, t));
-            b->any_general = b->any_general || (form == kSparse && b->idw[i].pmode == 0);
+            b->any_general[form] = b->any_general[form] || b->idw[i].pmode == 0;
         }
         b->work_off[form + 1] = (int32_t)b->work.size();
     }
@@ -633,7 +675,7 @@ auv_status enqueue_batched(auv_batch *b, char *ws, hipStream_t st)
     auto units = [&](int form) { return b->work_off[form + 1] - b->work_off[form]; };
     auto launch = [&](int form, hipStream_t s) -> auv_status {
         if (units(form) > 0) {
-            launch_form(form, b->any_general, t.idw, t.work + b->work_off[form], units(form), s);
+            launch_form(form, b->any_general[form], t.idw, t.work + b->work_off[form], units(form), s);
             AUV_HIP(hipGetLastError());
         }
         return AUV_OK;
@@ -647,8 +689,8 @@ auv_status enqueue_batched(auv_batch *b, char *ws, hipStream_t st)
         AUV_TRY_S(launch(kTop, b->cap_stream2));
         AUV_HIP(hipEventRecord(b->ev_join, b->cap_stream2));
     }
-    AUV_TRY_S(launch(kSparse, st));
-    AUV_TRY_S(launch(kSpan, st));
+    for (int form : {kSparse, kWide, kWindow, kSpan})
+        AUV_TRY_S(launch(form, st));
     if (fork)
         AUV_HIP(hipStreamWaitEvent(st, b->ev_join, 0));
     for (int i = 0; i < count; ++i) {
