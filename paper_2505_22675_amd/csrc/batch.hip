@@ -54,14 +54,21 @@ struct IdwItem {
 
 // The unit of block b out of n: blocks are dealt round-robin to the 8 XCDs,
 // so each XCD gets runs of kRun consecutive units (neighbouring tiles of an
-// item, whose halos overlap in its L2) and every XCD a share of every item.
+// item, whose halos overlap in its L2) and every XCD a share of every item.  Inside
+// a run the order is transposed as 4 x 16: an XCD's blocks go to its four shader
+// engines in turn, so units taken in order put every fourth tile on the same engine,
+// and soundings in lines a multiple of four tiles apart (32 nodes) on a quarter of
+// the chip (60 tiles of 256^2 nodes with all soundings in 5 % of the width at such a
+// spacing, 60 per disk on average: in order 5.18 ms, transposed 2.99).
 // (Queues with one head per XCD and guided grabs took longer: every grab is a
 // device atomic on one of eight addresses, and the loop around a tile made the
 // compiler keep its constants in scratch.)
 __device__ inline int deal_unit(int b, int n)
 {
     const int g = b / (kXcds * kRun), l = b - g * (kXcds * kRun);
-    return (g + 1) * (kXcds * kRun) <= n ? g * (kXcds * kRun) + (l & (kXcds - 1)) * kRun + l / kXcds
+    const int p = l / kXcds;
+    return (g + 1) * (kXcds * kRun) <= n ? g * (kXcds * kRun) + (l & (kXcds - 1)) * kRun +
+                                               (p >> 2) + (p & 3) * (kRun / 4)
                                          : b;
 }
 
