@@ -736,21 +736,34 @@ auv_status launch_kriging(const float *src, const auv_grid_desc &s, float *dst,
     // more rows per block reuse more covariance terms or weights, but a small
     // grid needs the blocks: halve (down to 8) while under 1024 blocks
     const int64_t ncb = (d.nx + kKrigCols - 1) / kKrigCols;
-    p.rows = phase ? kPhaseRows : kKrigRows;
-    while (p.rows > 8 && ncb * ((d.ny + p.rows - 1) / p.rows) < 1024)
-        p.rows /= 2;
+    auto block_rows = [&](int rows) {
+        while (rows > 8 && ncb * ((d.ny + rows - 1) / rows) < 1024)
+            rows /= 2;
+        return rows;
+    };
+    p.rows = block_rows(phase ? kPhaseRows : kKrigRows);
     // and the block's source rectangle has to fit kPhaseStage values, which
     // leave four blocks to a CU (two rows of slack for the rounding of the
-    // axis maps)
+    // axis maps); where eight rows do not, the other form takes its own rows
     const double sw = std::min((double)s.nx, std::ceil((kKrigCols - 1) * d.dx / s.dx) + 7.0);
     auto rect = [&](int rows) {
         return sw * std::min((double)s.ny, std::ceil((rows - 1) * d.dy / s.dy) + 7.0);
     };
-    while (phase && rect(p.rows) > kPhaseStage) {
-        if (p.rows > 8) {
-            p.rows /= 2;
-        } else {
+    while (phase && p.rows > 8 && rect(p.rows) > kPhaseStage)
+        p.rows /= 2;
+    if (phase) {
+        // Eight rows of half the source's spacing use each weight four times: with a
+        // rectangle that would not let them be sixteen, that pays only while the
+        // launch leaves CUs idle anyway (4000 x 1000 to 1333 x 2000, 1500 blocks, 33.5 us,
+        // the other form 27.4; 8000 x 4000 to 2758 x 8000, 162 and 115; 2000 x 1000 to
+        // 690 x 2000, 750 blocks, 16.9 and 17.4).  At the source's own spacing eight
+        // rows pay: 4000 x 2000 to 2000 x 2000, 33.6 and 48.9.
+        const int64_t blocks = ncb * ((d.ny + p.rows - 1) / p.rows);
+        const bool few_rows =
+            2.0 * d.dy < 1.5 * s.dy && rect(16) > kPhaseStage && blocks > 1024;
+        if (rect(p.rows) > kPhaseStage || few_rows) {
             phase = false;
+            p.rows = block_rows(kKrigRows);
         }
     }
     const size_t lds = phase ? sizeof(float) * (size_t)rect(p.rows) : 0;
