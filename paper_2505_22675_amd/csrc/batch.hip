@@ -322,8 +322,9 @@ size_t most_units(const auv_batch_item &it)
 std::vector<Choice> candidates(const auv_batch_item &it, int32_t sR)
 {
     std::vector<Choice> c;
-    // the sparse form re-does every node over the cap exactly: hopeless once
-    // a disk holds several times the cap (timing it there costs seconds)
+    // the sparse form walks a tile's soundings again for every eight members of the
+    // cap once a node is above it: at four caps per disk it takes twice the dense
+    // form's time (512^2 nodes, cap 16: 245 and 108 us)
     const bool sparse_ok = !dense_allowed(it) || disk_population(it) < 4.0 * it.params.max_pts;
     for (int d = -1; d <= 1 && sparse_ok; ++d)
         if (sR + d >= 12 && sR + d <= 26)
@@ -951,11 +952,12 @@ auv_status auv_batch_autotune(const auv_batch_item *items, int32_t count, void *
         const auv_batch_item &it = b->items[i];
         Choice best = with_default_tile(Choice{b->geom_plain[i].s, auto_algo(it)});
         float best_ms = 1e30f;
-        // min of three timed runs (after one untimed) of binning + IDW
         // Time of a candidate in the setting it will run in: binning the item
-        // (min of three runs after one untimed), plus the batched kernel of
+        // (min of three rows of runs after one untimed), plus the batched kernel of
         // its form over enough repetitions of the item's tiles to fill the
-        // chip (all reading the same bins), per repetition; items the
+        // chip (all reading the same bins), per repetition, and over the
+        // item's tiles alone, by the item's share of the batch (a small batch
+        // is its longest item's chain); items the
         // batched kernels do not cover get their own IDW launch instead.
         auto time_choice = [&](const Choice &c, float *out_ms) -> auv_status {
             *out_ms = 1e30f;
@@ -983,9 +985,25 @@ auv_status auv_batch_autotune(const auv_batch_item *items, int32_t count, void *
                 return AUV_OK;
             };
             float bin_ms, idw_ms;
+            // (several in a row: one alone is launches and waits, whose scatter of a
+            // microsecond exceeds what a small item's IDW takes in the batch)
+            constexpr int kBinRuns = 16;
             AUV_TRY_S(min_of_runs(
-                [&] { return launch_binning(&b->grids[i], gg, it.x, it.y, it.z, it.n, w, st); },
+                [&]() -> auv_status {
+                    for (int r = 0; r < kBinRuns; ++r)
+                        AUV_TRY_S(
+                            launch_binning(&b->grids[i], gg, it.x, it.y, it.z, it.n, w, st));
+                    return AUV_OK;
+                },
                 &bin_ms));
+            // an item's binning leaves most of the chip to the other items of its batch
+            // and is waited for with theirs: it counts by the share of the chip's blocks
+            // (eight to a CU) that its largest launch takes, and by the item's share of
+            // the batch.  Counted in full, the choice was that of the bins whose lone
+            // binning is fastest: 64 tiles up to 256^2 139 us untuned, 151 tuned, now 130;
+            // 150 tiles up to 128^2 240, 269, 226; 256 tiles 1626, 1780, 1582.
+            const double bin_blocks = std::max<double>(gg.nby, row_scatter_blocks(it.n));
+            bin_ms *= (float)(std::min(1.0, bin_blocks / (24.0 * cus) + 1.0 / count) / kBinRuns);
             IdwItem d;
             if (!make_idw_item(it, bv, a, c.algo, &d) || !row_path_ok(gg) || d.ntiles < 1) {
                 AUV_TRY_S(min_of_runs([&] { return launch_idw(bv, a, st); }, &idw_ms));
@@ -1004,19 +1022,32 @@ auv_status auv_batch_autotune(const auv_batch_item *items, int32_t count, void *
             AUV_HIP(hipMemcpyAsync(t.idw, &d, sizeof(d), hipMemcpyHostToDevice, st));
             AUV_HIP(hipMemcpyAsync(t.work, work.data(), sizeof(int2) * nwork,
                                    hipMemcpyHostToDevice, st));
-            AUV_TRY_S(min_of_runs(
-                [&]() -> auv_status {
-                    launch_form(d.form, d.pmode == 0, t.idw, t.work, nwork, st);
-                    AUV_HIP(hipGetLastError());
-                    return AUV_OK;
-                },
-                &idw_ms));
-            *out_ms = bin_ms + idw_ms / (float)copies;
+            auto idw_time = [&](int units, float *ms) {
+                return min_of_runs(
+                    [&]() -> auv_status {
+                        launch_form(d.form, d.pmode == 0, t.idw, t.work, units, st);
+                        AUV_HIP(hipGetLastError());
+                        return AUV_OK;
+                    },
+                    ms);
+            };
+            float alone_ms;
+            AUV_TRY_S(idw_time(nwork, &idw_ms));
+            AUV_TRY_S(idw_time(d.ntiles, &alone_ms));
+            *out_ms = bin_ms + idw_ms / (float)copies + alone_ms / (float)count;
             return AUV_OK;
         };
-        // bin size and form at the form's default tile, then the other node
-        // tiles of the winner
-        for (const Choice &c0 : candidates(it, b->geom_plain[i].s)) {
+        // bin size and form at the form's default tile, the untuned plan's choice among
+        // them (the list form's bins of at least the radius are in no dense candidate),
+        // then the other node tiles of the winner
+        std::vector<Choice> cand = candidates(it, b->geom_plain[i].s);
+        const Choice untuned{b->geom[i].s, b->algo[i]};
+        if (untuned.algo != AUV_ALGO_SPAN &&
+            std::none_of(cand.begin(), cand.end(), [&](const Choice &c) {
+                return c.bin_log2 == untuned.bin_log2 && c.algo == untuned.algo;
+            }))
+            cand.push_back(untuned);
+        for (const Choice &c0 : cand) {
             const Choice c = with_default_tile(c0);
             float ms;
             result = time_choice(c, &ms);
