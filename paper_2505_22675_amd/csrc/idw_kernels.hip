@@ -1,7 +1,8 @@
 // Radius-limited IDW and nearest-neighbour gridding on gfx950: the choice of
 // the kernel form, and the general tile kernel, which covers the calls that no
-// other form does (node lattices that are not linear, with caps above 64 or
-// ranking keys beyond 62 bits).
+// other form does (caps above 64 or ranking keys beyond 62 bits on node lattices
+// that are not linear, rows of more than 2^26 nodes or more than 2^28 soundings) and
+// requests for the span form on lattices that are not linear.
 //
 // One 64-lane wavefront (one workgroup) owns an 8x8 tile of grid nodes, one
 // node per lane.  The binned soundings of every bin row that meets the tile
@@ -403,8 +404,9 @@ auv_status launch_idw(const auv_bin_view &bv, const IdwArgs &a_in, hipStream_t s
     a.pmode = pmode;
     WinGeom wg;
     const bool linear = window_geometry(a, &wg);
-    // the window form addresses a tile's 16 rows by 32-bit byte offsets
-    const bool window = linear && a.nx <= 1 << 26;
+    // the window form addresses a tile's 16 rows and the 16-byte records by 32-bit
+    // byte offsets
+    const bool window = linear && a.nx <= 1 << 26 && bv.idx_bits <= 28;
     // The dense form: by the gather form's lists on bins of at least the radius and
     // up to some density, by its ring search on finer bins, where it stops after a
     // few small ones, and at higher densities.
