@@ -92,7 +92,10 @@ enum {
                             least max_pts / 2 (and 1 <= max_pts <= 32): many
                             nodes would exceed the cap; else sparse */
     AUV_ALGO_SPARSE = 1, /* every sounding within reach applied to each node */
-    AUV_ALGO_DENSE = 2,  /* per-node ring search with a register top-k list;
+    AUV_ALGO_DENSE = 2,  /* per-node register top-k list, by a ring search over
+                            the bins or (caps up to 16, bins of at least the
+                            radius, moderate densities) over every sounding
+                            within reach of a node tile;
                             needs 1 <= max_pts <= 32 and AUV_P_FP32_REBASE */
     AUV_ALGO_SPAN = 3    /* sparse, span form: (sounding, node) pairs packed 64
                             per instruction, LDS atomics; integer powers

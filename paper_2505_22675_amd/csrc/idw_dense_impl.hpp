@@ -208,8 +208,8 @@ __device__ __forceinline__ void dense_finish(const auv_bin_view &bv, const IdwAr
     }
 }
 
-// Exact value of node (row an, column b) by one lane (no wave-wide operations,
-// so any subset of lanes may call it): ring search for the max_pts nearest
+// Exact value of node (row an, column b) by one lane (any subset of lanes may call
+// it: the lanes only agree on how far the next rings reach): ring search for the max_pts nearest
 // keys (max_pts <= KMAX), then the weighted sum in key order.  Writes the
 // node's outputs.
 template <int kMode, int KMAX>

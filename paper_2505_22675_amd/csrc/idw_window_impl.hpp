@@ -534,8 +534,6 @@ __device__ void window_tile(const auv_bin_view &bv, const IdwArgs &a, const WinG
                             int tile, int ntx, const WinSmem &sm)
 {
     constexpr bool kIdw = (kMode & 1) != 0;
-    // the nearest key serves the nearest outputs, hits and the cap
-    constexpr bool kKey = kPacked;
     // Accumulators are updated by plain LDS read-modify-write: within one
     // instruction every lane owns a distinct node, and a wave's LDS operations
     // complete in order, so no atomics are needed (LDS atomics would serialise
@@ -604,8 +602,7 @@ __device__ void window_tile(const auv_bin_view &bv, const IdwArgs &a, const WinG
             s_lo[q] = INFINITY;
             s_hi[q] = -INFINITY;
             if constexpr (kPacked) {
-                if constexpr (kKey)
-                    s_key[q] = ~0ull;
+                s_key[q] = ~0ull;
             } else {
                 s_bd2[q] = 1e300;
                 s_bidx[q] = INT_MAX;
@@ -818,7 +815,7 @@ __device__ void window_tile(const auv_bin_view &bv, const IdwArgs &a, const WinG
                         mem = in && dv <= a.r2f;
                         d2f = dv * 0x1p32f;
                     }
-                    if constexpr (kExact && kKey && kIdw && kPmode != 0) {
+                    if constexpr (kExact && kPacked && kIdw && kPmode != 0) {
                         // The weight, key and addresses for every lane (a masked
                         // VALU instruction costs the same issue slot), so that
                         // the masked block below holds the LDS updates only and
@@ -876,13 +873,13 @@ __device__ void window_tile(const auv_bin_view &bv, const IdwArgs &a, const WinG
                         // atomics (no read back; lanes of one instruction hit
                         // distinct nodes, and a wave's LDS operations execute
                         // in program order, so the result is deterministic)
-                        if constexpr (kKey) {
+                        if constexpr (kPacked) {
                             const unsigned long long key =
                                 ((unsigned long long)D2 << kb) | (unsigned)sidx;
                             lds_min(reinterpret_cast<unsigned long long *>(
                                         reinterpret_cast<char *>(s_key) + q8),
                                     key);
-                        } else if constexpr (!kPacked) {
+                        } else {
                             const double d2 = (double)D2, bd = s_bd2[q];
                             if (d2 < bd || (d2 == bd && sidx < s_bidx[q])) {
                                 s_bd2[q] = d2;
@@ -971,14 +968,11 @@ __device__ void window_tile(const auv_bin_view &bv, const IdwArgs &a, const WinG
         const float lov = s_lo[q], hiv = s_hi[q];
         int bi;
         bool hit;
-        if constexpr (kKey) {
+        if constexpr (kPacked) {
             const unsigned long long key = s_key[q];
             asm volatile("" ::"v"(cnt), "v"(key), "v"(ndv.x), "v"(ndv.y), "v"(lov), "v"(hiv));
             bi = (int)(key & imask);
             hit = (key >> kb) == 0ull;
-        } else if constexpr (kPacked) {
-            bi = 0;
-            hit = false;
         } else {
             bi = s_bidx[q];
             hit = s_bd2[q] == 0.0;
