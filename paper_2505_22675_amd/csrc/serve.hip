@@ -354,6 +354,7 @@ struct auv_session {
     std::deque<auv::Pick> pending;
     std::deque<auv::Ticket> tickets;
     std::deque<auv::Launch> inflight;
+    bool launching = false;  // the worker has requests that are in neither queue
     bool stop = false;
     bool failed = false;
     std::string error;
@@ -627,6 +628,7 @@ void worker_main(auv_session *s)
             s->free_tables.pop_back();
             hipEvent_t ev = s->free_events.back();
             s->free_events.pop_back();
+            s->launching = true;
             lk.unlock();
             const auv_status st = enqueue_launch(s, picks, table, ev);
             const std::string msg = st == AUV_OK ? std::string() : std::string(auv_last_error());
@@ -641,6 +643,7 @@ void worker_main(auv_session *s)
                 s->error = "launch failed: " + msg;
             }
             s->inflight.push_back(Launch{picks, table, ev});
+            s->launching = false;
             if (st != AUV_OK) {
                 while (s->inflight.size() > 1)
                     complete_front(s, hipEventQuery(s->inflight.front().ev));
@@ -856,7 +859,7 @@ auv_status auv_session_drain(auv_session *s)
     if (!s)
         return fail(AUV_ERR_INVALID, "session is null");
     std::unique_lock<std::mutex> lk(s->mu);
-    s->cv_done.wait(lk, [&] { return s->pending.empty() && s->inflight.empty(); });
+    s->cv_done.wait(lk, [&] { return s->pending.empty() && s->inflight.empty() && !s->launching; });
     if (s->failed)
         return fail(AUV_ERR_HIP, s->error);
     return AUV_OK;
