@@ -5,9 +5,9 @@
 //   auv_batch_launch    first call: upload item tables, capture
 //                         batched binning (4 launches for all items)
 //                         -> one IDW launch per kernel form over the units of
-//                         all its items (sparse gather / dense top-k, on two
-//                         concurrent branches; span), + per-item launches for
-//                         items they do not cover
+//                         all its items (sparse gather, window, span / dense
+//                         top-k, on two concurrent branches), + per-item
+//                         launches for items they do not cover
 //                       into a HIP graph; later calls replay the graph
 //   auv_batch_launch_plain  the same items one after another, default sizes
 //   auv_batch_autotune  time (bin size, form) candidates per item class
@@ -79,7 +79,7 @@ __device__ inline int deal_unit(int b, int n)
 // per wave.  Bound by vector instruction issue like the gather form itself.
 // Against the persistent window kernel it replaced (LDS accumulators, work from
 // queues): 32 tiles of 512^2 nodes with 0.25 / 2 / 8 soundings per disk, binning
-// included, 699 / 716 / 912 -> 136 / 185 / 572 us (cap 16), 877 -> 385 us
+// included, 698 / 713 / 900 -> 108 / 138 / 417 us (cap 16), 864 -> 284 us
 // (8 per disk, no cap).
 template <bool kGeneral, bool kGen>
 __global__ __launch_bounds__(256, 8) void k_idw_batch_sparse(const IdwItem *__restrict__ items,

@@ -17,15 +17,14 @@
 // depths.  Sums are relative to the depth of the tile's first record.  A node
 // with coincident soundings (D^2 == 0) takes their mean depth.
 //
-// What bounds it: vector instruction issue on large grids (490 vector and 330
+// What bounds it: vector instruction issue on large grids (411 vector and 286
 // scalar instructions per 64 nodes of the 2M-sounding swath; a SIMD issues a
 // vector one in 4.2 clocks), the latency of one wave's chain of reads on small
 // ones.  Against the window form it replaces (16 x 16 nodes per wave, LDS
-// accumulators, over-cap nodes one at a time), on an MI355X, whole calls with
-// their binning when it came: 20k soundings on 256^2 nodes, 121-node disks 76 ->
-// 39 us; 150k swath soundings on 1023 x 769, cap 16, 71 -> 48 us; nearest only,
-// 500k on 2048 x 1500, 108 -> 84 us; against the tile kernel, 120k on 701 x 650 at
-// 3.3 m 89 -> 47 us.
+// accumulators, over-cap nodes one at a time), on an MI355X, without binning: 20k
+// soundings on 256^2 nodes, 121-node disks 53 -> 15.5 us; nearest only, 500k on 2048 x
+// 1500, 64 -> 37 us; the 2M-sounding swath 214 -> 175 us; against the tile kernel, 120k
+// on 701 x 650 at 3.3 m 61 -> 19 us.
 #pragma once
 #include "idw_dense_impl.hpp"
 #include "idw_window_impl.hpp"
@@ -570,8 +569,8 @@ constexpr int top_waves(int top) { return top == 8 ? 8 : 5; }
 // lists hold about half of that, and every record is read once per tile instead
 // of once per node.  Bound by vector instruction issue (the list merges) and, at
 // one wave generation, by the chain of a tile's batches.  512^2 nodes, disks of
-// (cap): 20 (16) 50 -> 46 us, 9 (16) 31 -> 26, 30 (16) 68 -> 59, 5 (8) 23 -> 14, 20 (8)
-// 47 -> 31; finer bins, caps above 16 and dense disks keep the ring search
+// (cap): 20 (16) 44 -> 39 us, 9 (16) 30 -> 23, 30 (16) 59 -> 54, 5 (8) 20 -> 12, 20 (8)
+// 42 -> 28; finer bins, caps above 16 and dense disks keep the ring search
 // (gather_top_pays).
 template <int kMode, int kTop, bool kGen>
 __global__ __launch_bounds__(64, top_waves(kTop)) void k_idw_gather_top(auv_bin_view bv, IdwArgs a,

@@ -366,15 +366,15 @@ namespace {
 // Many almost empty tiles: the window form's cover four times the nodes, and a
 // wave's chain of waits is all that such a tile costs.  Nearest pick at 0.1, 0.3, 1
 // and 4 soundings per disk of 3 spacings, spread evenly, gather / window: 4096^2
-// nodes 71 / 54, 88 / 64, 120 / 97, 271 / 398 us, 2048^2 21 / 16, 25 / 18, 35 / 29,
-// 77 / 117, 1024^2 8 / 7, 9 / 7, 12 / 10, 24 / 33; gathered in stripes on a tenth
-// of the grid, 4096^2 77 / 46, 81 / 61, 99 / 114 at 0.1, 0.3 and 1, 2048^2 25 / 19,
-// 27 / 28, 33 / 57.  The bound, four soundings expected within reach of an 8 x 8
-// tile, is 0.6 per disk there; up to 1.7 per disk evenly spread soundings would
-// be a little faster by windows, clustered ones half as fast.
+// nodes 85 / 71, 107 / 88, 133 / 121, 166 / 270 us, 2048^2 25 / 21, 31 / 25, 37 / 35,
+// 46 / 76, 1024^2 9 / 8, 10 / 9, 12 / 12, 16 / 24; all in stripes on a tenth of the
+// grid, 4096^2 72 / 46, 75 / 61, 92 / 114 at 0.1, 0.3 and 1, 2048^2 23 / 19, 25 / 27,
+// 31 / 57.  The bound, four soundings expected within reach of an 8 x 8 tile, is
+// 0.6 per disk there; up to 1.5 per disk evenly spread soundings would be up to a
+// tenth faster by windows, clustered ones half as fast.
 //
 // More than 64 bin rows per tile: the gather form reads them 64 at a time, each a
-// wait of its own (1000^2 nodes at 16 m, radius 0.32 m, 100k soundings 171 / 95 us).
+// wait of its own (1000^2 nodes at 16 m, radius 0.32 m, 100k soundings 170 / 95 us).
 bool window_pays(const auv_bin_view &bv, const IdwArgs &a, const WinGeom &g)
 {
     if (a.max_pts > 0 && a.mode != 2)
@@ -415,9 +415,10 @@ auv_status launch_idw(const auv_bin_view &bv, const IdwArgs &a_in, hipStream_t s
     if (a.dense)
         return launch_idw_dense(bv, a, pmode, st);
     // The gather form takes every exact call that it covers, but for a few on
-    // linear lattices: at 20k to 2M soundings it was measured faster than the window
-    // form there (1.02 to 1.9 times) and than the tile kernel on the others (1.9
-    // times).
+    // linear lattices: at 20k to 2M soundings it is faster than the window form there
+    // (1.2 to 3.4 times: 2M-sounding swath 214 -> 175 us, nearest of 500k 64 -> 37, 20k
+    // on 256^2 53 -> 15.5) and than the tile kernel on the others (120k on 701 x 650 at
+    // 3.3 m 61 -> 19).
     if (!a.span && gather_covers(bv, a) && !(window && window_pays(bv, a, wg)))
         return launch_idw_gather(bv, a, linear ? &wg : nullptr, st);
     if (window || (linear && a.precision != AUV_P_FP32_REBASE))
